@@ -1,18 +1,19 @@
 #!/usr/bin/env python3
 """Throughput of costa_transform on one MI355X.
 
-One step = one costa_transform (or costa_transform_batched) call: the direct
-path, then pack and unpack-transform of every wave, over synthetic seeded
-inputs already resident in HBM.  The plan (grid overlay, volume kernel,
-relabeling, rectangles) is built before the timed region and cached.
+One step = one costa_transform (or costa_transform_batched) call over
+synthetic seeded inputs already resident in HBM.  The plan (grid overlay,
+volume kernel, relabeling, rectangles) is built before the timed region and
+cached.
 
-Metric: effective GB/s = model bytes per step / time per step, with model
-bytes = read B + read A (beta != 0) + write A + 2 x message bytes (each
-message element is written by the pack and read by the unpack).
+Metric: effective GB/s = bytes per step / time per step, with bytes = read B +
+read A (beta != 0) + write A: the call takes the direct form, which has no
+message traffic.
 
 Also reported: the median and minimum step time (events between the timed
-steps), and the bytes a transform without message staging would move
-(read B + read A if beta != 0 + write A).
+steps), and under `message_form` the same steps through message buffers
+(pack, unpack-transform), whose model bytes add 2 x message bytes (each
+message element is written by the pack and read by the unpack).
 
 Prints one JSON line.  The default workload is the ScaLAPACK-style block-size
 change: fp64 16384 x 16384, 4x4 process grid, 128x128 -> 256x256 blocks,
@@ -94,7 +95,7 @@ def host_cpus() -> dict:
     return {"nproc": os.cpu_count() or 1, "affinity": affinity, "cpu": _cpu_model()}
 
 
-def cpu_baseline(w, sigma, model_bytes_per_elem: float, target_s: float, threads: int):
+def cpu_baseline(w, sigma, bytes_per_elem: float, target_s: float, threads: int):
     """The CPU oracle on bands of target rows, run by `threads` threads at once
     (the oracle's C loop runs outside the GIL).  Pairs of a batch are taken one
     after another, each for an equal share of `target_s`, with only that pair's
@@ -157,7 +158,7 @@ def cpu_baseline(w, sigma, model_bytes_per_elem: float, target_s: float, threads
     what = (f"bands of target rows of the {it0.A.nrows}x{it0.A.ncols} matrix" if len(w.items) == 1 else
             f"each of the {len(w.items)} pairs in turn for {per_item_s:.1f} s, only its buffers in host memory; "
             f"bands of target rows of its {it0.A.nrows}x{it0.A.ncols} matrix")
-    return {"value": round(total_elems * model_bytes_per_elem / total_s / 1e9, 4), "unit": "GB/s",
+    return {"value": round(total_elems * bytes_per_elem / total_s / 1e9, 4), "unit": "GB/s",
             "cores": threads, "kind": "oracle",
             "sample": f"{total_elems} elements of A ({what}, handed out in order; "
                       f"{', '.join(f'{p:.2f}' for p in passes)} passes over the matrix) in {total_s:.1f} s by "
@@ -449,7 +450,7 @@ def summarize_profiles(src: str, out_dir: str = None) -> None:
         for kind, k in d.get("kernels", {}).items():
             lines.append(f"- {kind}: {k['ms_per_launch'] * 1000:.1f} us per launch, {k['bytes_per_launch']} "
                          f"algorithmic bytes -> {k['GB_s']} GB/s ({k['launches_per_step']:g} launches per step)")
-        lines.append(f"- whole step: {d['ms_per_step']} ms for {d['model_bytes_per_step']} model bytes -> "
+        lines.append(f"- whole step: {d['ms_per_step']} ms for {d['bytes_per_step']} bytes -> "
                      f"{d['value']} GB/s ({d['pct_of_hbm_peak']}% of 8 TB/s)")
         r = d["roofline"]
         lines += [f"- roofline (dominant kernel {r['kernel']}): {r['achieved']} of {r['peak']:g} GB/s, "
@@ -692,17 +693,15 @@ def run_workload(name: str, args, cpu_seconds: float) -> dict:
     torch.cuda.empty_cache()
     cpu = None
     if cpu_seconds > 0:
-        cpu = cpu_baseline(w, sigma, stats["model_bytes"] / stats["total_elems"], cpu_seconds,
+        cpu = cpu_baseline(w, sigma, direct_bytes(stats) / stats["total_elems"], cpu_seconds,
                            max(1, args.cpu_threads))
     rec = {"value": m["value"], "unit": "GB/s", "ms_per_step": m["ms_per_step"],
            "pct_of_hbm_peak": round(100 * m["value"] / HBM_PEAK_GBS, 2), "dtype": w.dtype,
            "config": describe(w),
            "ms_per_step_median": m["ms_per_step_median"], "ms_per_step_min": m["ms_per_step_min"],
            "ms_per_step_max": m["ms_per_step_max"],
-           "model_bytes_per_step": stats["model_bytes"],
-           "bytes_without_staging_per_step": stats["model_bytes"] - 2 * stats["message_bytes"],
+           "bytes_per_step": direct_bytes(stats), "message_form": m["message_form"],
            "local_fraction": round(stats["local_elems"] / stats["total_elems"], 6),
-           "waves": m["kernels"].get("pack", {}).get("launches_per_step", 0),
            "plan_s": round(t_setup + m["first_step_s"], 3),
            "kernels": m["kernels"], "roofline": m["roofline"], "cpu_baseline": cpu}
     if name in NO_BANDWIDTH_CLAIM:
@@ -782,9 +781,8 @@ def main():
            "warmup": args.warmup, "ms_per_step": head["ms_per_step"], "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": head["dtype"], "data": "synthetic",
            "pct_of_hbm_peak": head["pct_of_hbm_peak"], "config": head["config"]}
-    for k in ("ms_per_step_median", "ms_per_step_min", "ms_per_step_max", "model_bytes_per_step",
-              "bytes_without_staging_per_step",
-              "local_fraction", "waves", "plan_s", "kernels", "roofline", "copy_ceiling", "cpu_baseline"):
+    for k in ("ms_per_step_median", "ms_per_step_min", "ms_per_step_max", "bytes_per_step", "message_form",
+              "local_fraction", "plan_s", "kernels", "roofline", "copy_ceiling", "cpu_baseline"):
         if k in head:
             out[k] = head[k]
     if len(names) > 1:
@@ -795,13 +793,56 @@ def main():
     print(json.dumps(out), flush=True)
 
 
+def direct_bytes(stats: dict) -> int:
+    """Bytes of a step in the direct form: read B, read A if beta != 0, write A."""
+    return stats["model_bytes"] - 2 * stats["message_bytes"]
+
+
+def timed_steps(step, steps: int) -> dict:
+    """`steps` steps: an event on the launch stream after each, the library's
+    per-launch events inside (in the form the caller enabled), and the wall
+    clock around all of them."""
+    import torch
+    import paper_2106_06601_amd as C
+    stream = torch.cuda.current_stream()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(steps + 1)]
+    # no garbage collection inside the timed steps: a full collection of the
+    # objects earlier workloads left holds the host for tens of ms, long
+    # enough for the GPU to run out of queued steps
+    gc.collect()
+    gc_was_on = gc.isenabled()
+    gc.disable()
+    try:
+        torch.cuda.synchronize()
+        wall0 = time.perf_counter()
+        ev[0].record(stream)
+        for i in range(steps):
+            step()
+            ev[i + 1].record(stream)
+        torch.cuda.synchronize()
+        wall = time.perf_counter() - wall0
+    finally:
+        if gc_was_on:
+            gc.enable()
+    kt = C.costa_timing_read()
+    kernels = {}
+    for k in KINDS:
+        d = kt[k]
+        if d["launches"]:
+            kernels[k] = {"launches_per_step": d["launches"] / steps,
+                          "ms_per_launch": round(d["ms"] / d["launches"], 5),
+                          "bytes_per_launch": d["bytes"] // d["launches"],
+                          "GB_s": round(d["bytes"] / (d["ms"] * 1e-3) / 1e9, 1)}
+    return {"ms_per_step": max(ev[0].elapsed_time(ev[-1]), wall * 1e3) / steps, "kernels": kernels,
+            "per_step": sorted(ev[i].elapsed_time(ev[i + 1]) for i in range(steps))}
+
+
 def measure(step, stats: dict, workload: str, args) -> dict:
-    """Warm-up, then `args.steps` timed steps: per-launch HIP events on the
-    launch stream plus one event pair around all steps."""
+    """Warm-up, then `args.steps` timed steps; after them the message form of
+    the same step (at most 20 steps of it)."""
     import torch
     import paper_2106_06601_amd as C
     dev = torch.device("cuda:0")
-    stream = torch.cuda.current_stream()
     if args.copy_probe:
         src = torch.ones(args.copy_probe << 17, dtype=torch.float64, device=dev)
         dst = torch.empty_like(src)
@@ -816,51 +857,28 @@ def measure(step, stats: dict, workload: str, args) -> dict:
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-
-    C.costa_timing_enable(True)
-    ev = [torch.cuda.Event(enable_timing=True) for _ in range(args.steps + 1)]
-    # no garbage collection inside the timed steps: a full collection of the
-    # objects earlier workloads left holds the host for tens of ms, long
-    # enough for the GPU to run out of queued steps
-    gc.collect()
-    gc_was_on = gc.isenabled()
-    gc.disable()
-    try:
-        torch.cuda.synchronize()
-        wall0 = time.perf_counter()
-        ev[0].record(stream)
-        for i in range(args.steps):
-            step()
-            ev[i + 1].record(stream)
-        torch.cuda.synchronize()
-        wall = time.perf_counter() - wall0
-    finally:
-        if gc_was_on:
-            gc.enable()
-    kt = C.costa_timing_read()
-    C.costa_timing_enable(False)
-    gpu_ms = ev[0].elapsed_time(ev[-1])
-    per_step = sorted(ev[i].elapsed_time(ev[i + 1]) for i in range(args.steps))
-    ms_per_step = max(gpu_ms, wall * 1e3) / args.steps
-    value = stats["model_bytes"] / (ms_per_step * 1e-3) / 1e9
-
-    per_kernel = {}
-    for k in KINDS:
-        d = kt[k]
-        if d["launches"]:
-            per_kernel[k] = {"launches_per_step": d["launches"] / args.steps,
-                             "ms_per_launch": round(d["ms"] / d["launches"], 5),
-                             "bytes_per_launch": d["bytes"] // d["launches"],
-                             "GB_s": round(d["bytes"] / (d["ms"] * 1e-3) / 1e9, 1)}
-    dominant = max(per_kernel, key=lambda k: kt[k]["ms"])
-    dk = per_kernel[dominant]
+    C.costa_timing_enable(C.TIMING_AS_CALLED)
+    t = timed_steps(step, args.steps)
+    value = direct_bytes(stats) / (t["ms_per_step"] * 1e-3) / 1e9
+    dk = t["kernels"]["direct"]
     achieved = dk["GB_s"]
-    traffic = load_traffic(workload, dominant, dk["launches_per_step"])
-    roof = {"bound": "hbm", "kernel": dominant, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
+    roof = {"bound": "hbm", "kernel": "direct", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(achieved / HBM_PEAK_GBS, 4),
+            "traffic": load_traffic(workload, "direct", dk["launches_per_step"]),
             "bytes_per_launch": dk["bytes_per_launch"], "ms_per_launch": dk["ms_per_launch"]}
-    return {"value": round(value, 1), "ms_per_step": round(ms_per_step, 4), "kernels": per_kernel,
-            "roofline": roof, "first_step_s": first_step_s,
+
+    C.costa_timing_enable(C.TIMING_MESSAGES)
+    for _ in range(1 + min(args.warmup, 3)):
+        step()
+    C.costa_timing_enable(C.TIMING_MESSAGES)  # counters of the timed steps only
+    msg = timed_steps(step, min(args.steps, 20))
+    C.costa_timing_enable(False)
+    per_step = t["per_step"]
+    return {"value": round(value, 1), "ms_per_step": round(t["ms_per_step"], 4),
+            "kernels": {**msg["kernels"], **t["kernels"]}, "roofline": roof, "first_step_s": first_step_s,
+            "message_form": {"ms_per_step": round(msg["ms_per_step"], 4), "model_bytes_per_step": stats["model_bytes"],
+                             "GB_s": round(stats["model_bytes"] / (msg["ms_per_step"] * 1e-3) / 1e9, 1),
+                             "waves": msg["kernels"].get("pack", {}).get("launches_per_step", 0)},
             "ms_per_step_median": round(per_step[len(per_step) // 2], 4), "ms_per_step_min": round(per_step[0], 4),
             "ms_per_step_max": round(per_step[-1], 4)}
 
@@ -967,8 +985,7 @@ def scalapack_bench(name: str, args) -> dict:
                        "target": dsc(call.C) + f", submatrix at ({call.ic}, {call.jc})"},
             "ms_per_step_median": m["ms_per_step_median"], "ms_per_step_min": m["ms_per_step_min"],
             "ms_per_step_max": m["ms_per_step_max"],
-            "model_bytes_per_step": stats["model_bytes"],
-            "bytes_without_staging_per_step": stats["model_bytes"] - 2 * stats["message_bytes"],
+            "bytes_per_step": direct_bytes(stats), "message_form": m["message_form"],
             "local_fraction": round(stats["local_elems"] / stats["total_elems"], 6),
             "kernels": m["kernels"], "roofline": m["roofline"]}
 

@@ -9,11 +9,19 @@
  * between two arbitrary grid layouts of the same P processes (Section 5,
  * "Matrix Layout"; Section 6, Figure 1).  On one GPU the P processes are
  * P virtual ranks: each rank's local matrix is a separate device buffer.
- * The exchange of packages between ranks (Algorithm 3) becomes a pack of the
- * remote blocks into per-(sender, receiver) message buffers in HBM and an
- * unpack-transform out of them; blocks whose sender is also their (relabeled)
- * receiver take a direct path without a message buffer (Section 6,
- * "Overlap of Communication and Computation").
+ * A transform runs in one of two forms with the same results bit for bit:
+ *   - the direct form, the default: every block goes straight from B to A, in
+ *     one pass over both (both ends of every package are in the same memory);
+ *   - the message form: the exchange of packages between ranks (Algorithm 3)
+ *     as a pack of the remote blocks into per-(sender, receiver) message
+ *     buffers in HBM and an unpack-transform out of them; blocks whose sender
+ *     is also their (relabeled) receiver take the direct path (Section 6,
+ *     "Overlap of Communication and Computation").  Calls take it while a
+ *     workspace limit is set (costa_set_workspace_limit) or the message
+ *     kernels are timed (costa_timing_enable), and when an A buffer shares
+ *     memory with a B buffer.
+ * costa_plan_stats() and costa_plan_export() describe the message form (the
+ * packages and what they cost).
  *
  * Conventions used throughout:
  *   - Every call returns a costa_status; nothing throws across the boundary.
@@ -287,12 +295,15 @@ costa_status costa_transform_batched(costa_dtype dtype, int32_t n, const costa_t
 costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32_t n, const costa_transform_desc* desc,
                                              const int32_t* sigma, hipStream_t stream);
 
-/* Caps the message-buffer workspace.  A plan whose messages exceed the cap
- * is executed in waves (pack + unpack per wave).  0 = automatic (a share of
- * the free device memory at planning time).  Affects plans built afterwards. */
+/* Caps the message-buffer workspace: later transforms run in the message
+ * form, and a plan whose messages exceed the cap in waves (pack + unpack per
+ * wave).  0 (the default) = no limit set: the direct form, which needs no
+ * workspace, and in calls that take the message form all the same a workspace
+ * of a share of the free device memory at planning time.  Affects plans built
+ * afterwards. */
 costa_status costa_set_workspace_limit(size_t bytes);
 
-/* Statistics of the plan a transform with these arguments would use. */
+/* Statistics of the message form of a transform with these arguments. */
 typedef struct {
   int64_t total_elems;       /* sum over pairs of nrows*ncols */
   int64_t local_elems;       /* elements on the direct path (sender == receiver) */
@@ -341,8 +352,8 @@ typedef struct {
   int64_t wide_ntasks;    /* tasks of the wide table that move it (0 if none) */
 } costa_piece_info;
 
-/* Writes the rectangles of the plan a transform with these arguments would
- * use, in launch order (DIRECT, then PACK and UNPACK of each wave; a DIRECT
+/* Writes the rectangles of the message form of a transform with these
+ * arguments, in launch order (DIRECT, then PACK and UNPACK of each wave; a DIRECT
  * or UNPACK step that holds both transposed and other rectangles is two
  * launches, the transposed ones first), into
  * out[0..capacity); *count = their total number (call with capacity 0 to
@@ -419,7 +430,11 @@ typedef struct {
 
 /* on != 0: bracket every later launch with HIP events (2048 of them are
  * created here, on the current device, so that the timed calls do not create
- * them).  Resets the counters. */
+ * them).  Resets the counters.  COSTA_TIMING_AS_CALLED times transforms in
+ * the form they run in untimed; any other value but 0 runs them in the
+ * message form, whose pack and unpack-transform kernels the counters name. */
+#define COSTA_TIMING_MESSAGES 1
+#define COSTA_TIMING_AS_CALLED 2
 costa_status costa_timing_enable(int on);
 /* Waits for the recorded events, adds up their durations, returns the totals
  * since costa_timing_enable and keeps counting. */

@@ -104,6 +104,7 @@ _SIGS = {
     "costa_set_workspace_limit": [ctypes.c_size_t],
     "costa_plan_stats": [ctypes.c_int, _i32, _vp, _vp, _P(CostaStats)],
     "costa_plan_export": [ctypes.c_int, _i32, _vp, _vp, _vp, _i64, _P(_i64)],
+    "costa_plan_export_direct": [ctypes.c_int, _i32, _vp, _vp, _vp, _i64, _P(_i64)],
     "costa_timing_enable": [ctypes.c_int],
     "costa_timing_read": [_P(CostaTiming)],
     "costa_finalize": [],
@@ -397,19 +398,30 @@ def costa_plan_stats(dtype: str, descs: Sequence[dict], sigma=None) -> dict:
     return {name: getattr(st, name) for name, _ in CostaStats._fields_}
 
 
-def costa_plan_export(dtype: str, descs: Sequence[dict], sigma=None) -> np.ndarray:
-    """The plan's rectangles in launch order, as a numpy structured array."""
+def _plan_export(name: str, dtype: str, descs: Sequence[dict], sigma) -> np.ndarray:
     keep: List = []
     arr = (CostaDesc * len(descs))(*[_desc(dtype, d["op"], d.get("alpha"), d.get("beta"), d["A"], None, d["B"],
                                            None, keep) for d in descs])
     s, sp = _sigma(sigma)
     cnt = _i64()
-    _check(_lib.costa_plan_export(DTYPES[dtype], len(descs), ctypes.cast(arr, _vp), sp, None, 0,
-                                  ctypes.byref(cnt)), "costa_plan_export")
+    f = getattr(_lib, name)
+    _check(f(DTYPES[dtype], len(descs), ctypes.cast(arr, _vp), sp, None, 0, ctypes.byref(cnt)), name)
     out = (CostaPieceInfo * max(1, cnt.value))()
-    _check(_lib.costa_plan_export(DTYPES[dtype], len(descs), ctypes.cast(arr, _vp), sp, ctypes.cast(out, _vp),
-                                  cnt.value, ctypes.byref(cnt)), "costa_plan_export")
+    _check(f(DTYPES[dtype], len(descs), ctypes.cast(arr, _vp), sp, ctypes.cast(out, _vp), cnt.value,
+             ctypes.byref(cnt)), name)
     return np.ctypeslib.as_array(out)[:cnt.value].copy()
+
+
+def costa_plan_export(dtype: str, descs: Sequence[dict], sigma=None) -> np.ndarray:
+    """The rectangles of the message form in launch order, as a numpy
+    structured array."""
+    return _plan_export("costa_plan_export", dtype, descs, sigma)
+
+
+def costa_plan_export_direct(dtype: str, descs: Sequence[dict], sigma=None) -> np.ndarray:
+    """The rectangles of the direct form in launch order (an inspection call
+    of the library that its public header does not declare)."""
+    return _plan_export("costa_plan_export_direct", dtype, descs, sigma)
 
 
 # ---------------------------------------------------------------------------
@@ -476,8 +488,12 @@ def costa_set_workspace_limit(nbytes: int) -> None:
     _check(_lib.costa_set_workspace_limit(nbytes), "costa_set_workspace_limit")
 
 
+TIMING_MESSAGES, TIMING_AS_CALLED = 1, 2
+
+
 def costa_timing_enable(on: bool = True) -> None:
-    _check(_lib.costa_timing_enable(1 if on else 0), "costa_timing_enable")
+    """on: False, True (TIMING_MESSAGES) or TIMING_AS_CALLED."""
+    _check(_lib.costa_timing_enable(2 if on == TIMING_AS_CALLED else 1 if on else 0), "costa_timing_enable")
 
 
 def costa_timing_read() -> dict:

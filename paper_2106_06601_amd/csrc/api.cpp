@@ -1,6 +1,6 @@
 // C ABI entry points: volume matrix, transform, batched transform, plan
 // statistics, workspace control and kernel timing.  Plans are cached per
-// (device, element size, layouts, ops, relabeling, workspace cap).
+// (device, form, element size, layouts, ops, relabeling, workspace cap).
 #include <algorithm>
 #include <chrono>
 #include <cstring>
@@ -87,7 +87,7 @@ struct State {
   std::map<std::string, std::unique_ptr<DevicePlan>> plans;
   std::map<std::string, std::unique_ptr<HostPlan>> host_plans;  // plan statistics without a device
   std::map<int, Workspace> ws;
-  bool timing = false;
+  int timing = 0;  // COSTA_TIMING_MESSAGES, COSTA_TIMING_AS_CALLED or 0 (off)
   std::vector<TimingRec> pending;
   std::map<int, std::vector<hipEvent_t>> event_pool;  // per device: events are recorded on that device's streams
   costa_timing totals{};
@@ -98,11 +98,17 @@ State& state() {
   return *s;
 }
 
-std::string plan_key(int device, int es, const std::vector<ItemDesc>& items, const std::vector<int32_t>& sigma,
-                     size_t cap) {
+// The two forms of a transform, with the same results bit for bit.
+// FORM_DIRECT: every block goes straight from B to A.  FORM_MESSAGES: remote
+// blocks go through the message buffers (pack, then unpack-transform).
+enum Form : char { FORM_DIRECT = 0, FORM_MESSAGES = 1 };
+
+std::string plan_key(int device, Form form, int es, const std::vector<ItemDesc>& items,
+                     const std::vector<int32_t>& sigma, size_t cap) {
   std::string k;
   auto put = [&](const void* p, size_t n) { k.append(reinterpret_cast<const char*>(p), n); };
   put(&device, sizeof device);
+  put(&form, sizeof form);
   put(&es, sizeof es);
   put(&cap, sizeof cap);
   size_t n = items.size();
@@ -121,8 +127,9 @@ std::string plan_key(int device, int es, const std::vector<ItemDesc>& items, con
   return k;
 }
 
-PlanConfig make_config(int es) {
+PlanConfig make_config(int es, Form form) {
   PlanConfig c;
+  c.messages = form == FORM_MESSAGES;
   c.elem_size = es;
   c.workspace_cap = INT64_MAX;
   c.max_piece_elems = kMaxPieceElems;
@@ -337,12 +344,10 @@ int64_t auto_cap(State& S, int device, int64_t needed) {
   return std::min(needed, cap);
 }
 
-costa_status get_plan(State& S, costa_dtype dt, const std::vector<ItemDesc>& items, const std::vector<int32_t>& sig,
-                      DevicePlan*& out) {
-  int device = 0;
-  HIP_OR_FAIL(hipGetDevice(&device));
+costa_status get_plan(State& S, int device, Form form, costa_dtype dt, const std::vector<ItemDesc>& items,
+                      const std::vector<int32_t>& sig, DevicePlan*& out) {
   const int es = elem_size(dt);
-  std::string key = plan_key(device, es, items, sig, S.workspace_limit);
+  std::string key = plan_key(device, form, es, items, sig, S.workspace_limit);
   auto it = S.plans.find(key);
   if (it != S.plans.end()) {
     out = it->second.get();
@@ -355,7 +360,7 @@ costa_status get_plan(State& S, costa_dtype dt, const std::vector<ItemDesc>& ite
   std::unique_ptr<DevicePlan> dp(new (std::nothrow) DevicePlan());
   if (!dp) return fail(COSTA_ERROR_OUT_OF_MEMORY, "host allocation failed");
   dp->device = device;
-  PlanConfig cfg = make_config(es);
+  PlanConfig cfg = make_config(es, form);
   try {
     build_plan(items, sig, cfg, [&](int64_t need) { return auto_cap(S, device, need); }, dp->host);
   } catch (const std::bad_alloc&) {
@@ -421,6 +426,37 @@ size_t call_table(costa_dtype dt, int32_t n, const costa_transform_desc* desc, i
   return ptr_bytes;
 }
 
+// Whether some A buffer of the call shares memory with some B buffer (by the
+// bytes their layouts reach).  Such calls take the message form: the pack
+// reads every remote block of a wave before the unpack writes any of A, as it
+// always has for them (a grid's ranks that swap blocks within one set of
+// buffers, or a submatrix copied inside one matrix).
+bool a_overlaps_b(int es, int32_t n, const costa_transform_desc* desc, const std::vector<ItemDesc>& items,
+                  const std::vector<int32_t>& sig, int32_t P) {
+  struct Range {
+    uintptr_t lo, hi;
+    bool is_a;
+  };
+  std::vector<Range> v;
+  v.reserve((size_t)2 * n * P);
+  for (int32_t k = 0; k < n; ++k)
+    for (int32_t t = 0; t < P; ++t) {
+      const int32_t r = sig.empty() ? t : sig[t];
+      const uintptr_t na = (uintptr_t)items[k].A->local_elems[t] * es, nb = (uintptr_t)items[k].B->local_elems[t] * es;
+      const uintptr_t a = (uintptr_t)desc[k].A_local[r], b = (uintptr_t)desc[k].B_local[t];
+      if (na) v.push_back(Range{a, a + na, true});
+      if (nb) v.push_back(Range{b, b + nb, false});
+    }
+  std::sort(v.begin(), v.end(), [](const Range& x, const Range& y) { return x.lo < y.lo; });
+  uintptr_t end_a = 0, end_b = 0;  // the furthest end so far of either kind
+  for (const Range& r : v) {
+    if (r.lo < (r.is_a ? end_b : end_a)) return true;
+    uintptr_t& end = r.is_a ? end_a : end_b;
+    end = std::max(end, r.hi);
+  }
+  return false;
+}
+
 // Enqueues every launch of a plan: the direct path (when not merged), then
 // pack and unpack-transform of each wave.
 costa_status launch_plan(State& S, costa_dtype dt, const HostPlan& hp, const DeviceTables& tabs,
@@ -463,20 +499,35 @@ costa_status transform_impl(costa_dtype dt, int32_t n, const costa_transform_des
   int64_t total = 0;
   for (const ItemDesc& d : items) total += d.A->nrows * d.A->ncols;
   if (total == 0) return COSTA_SUCCESS;
-  DevicePlan* dp = nullptr;
-  st = get_plan(S, dt, items, sig, dp);
-  if (st != COSTA_SUCCESS) return st;
-  const HostPlan& hp = dp->host;
+  int device = 0;
+  HIP_OR_FAIL(hipGetDevice(&device));
   const int32_t P = items[0].A->nranks;
-
-  Workspace* ws = nullptr;
-  st = ensure_workspace(S, dp->device, (size_t)hp.workspace_bytes, ws);
-  if (st != COSTA_SUCCESS) return st;
-
   std::vector<unsigned char> table;
   std::vector<char> reads_a;
   bool aligned = true;
-  const size_t ptr_bytes = call_table(dt, n, desc, P, ws->ptr, table, reads_a, aligned);
+  const size_t ptr_bytes = call_table(dt, n, desc, P, nullptr, table, reads_a, aligned);
+
+  // The direct form moves each element once; the message form (pack,
+  // unpack-transform) moves remote ones twice and is for the callers that ask
+  // for its buffers or its kernels' times, and for overlapping buffers.
+  // Measured on MI355X, messages against direct: the fp64 16384^2 block-size
+  // change 1153 -> 664 us, the complex 16384^2 case 2832 -> 1539, a 320 x 200
+  // one 23 -> 15.5 (a launch less); no shape was faster in messages.
+  Form form = S.timing == COSTA_TIMING_MESSAGES || S.workspace_limit ? FORM_MESSAGES : FORM_DIRECT;
+  if (form == FORM_DIRECT && a_overlaps_b(elem_size(dt), n, desc, items, sig, P)) form = FORM_MESSAGES;
+  DevicePlan* dp = nullptr;
+  st = get_plan(S, device, form, dt, items, sig, dp);
+  if (st != COSTA_SUCCESS) return st;
+  const HostPlan& hp = dp->host;
+
+  // message buffers, shared by every call on this device: order after the last user
+  Workspace* ws = nullptr;
+  if (hp.workspace_bytes) {
+    st = ensure_workspace(S, dp->device, (size_t)hp.workspace_bytes, ws);
+    if (st != COSTA_SUCCESS) return st;
+    reinterpret_cast<void**>(table.data())[(size_t)2 * n * P] = ws->ptr;
+    if (ws->used && ws->last_stream != stream) HIP_OR_FAIL(hipStreamWaitEvent(stream, ws->last_use, 0));
+  }
   if (table != dp->last_table) {
     // the kernels of the plan's last call read the table until they end: on
     // another stream, the new table is written only after them
@@ -488,8 +539,6 @@ costa_status transform_impl(costa_dtype dt, int32_t n, const costa_transform_des
     dp->table_pending = true;
     dp->last_table.swap(table);
   }
-  // message buffers are shared by every call on this device: order after the last user
-  if (ws->used && ws->last_stream != stream) HIP_OR_FAIL(hipStreamWaitEvent(stream, ws->last_use, 0));
 
   void* const* d_bufs = reinterpret_cast<void* const*>(dp->d_table);
   const ItemParam* d_items = reinterpret_cast<const ItemParam*>((unsigned char*)dp->d_table + ptr_bytes);
@@ -497,7 +546,7 @@ costa_status transform_impl(costa_dtype dt, int32_t n, const costa_transform_des
   st = launch_plan(S, dt, hp, DeviceTables{dp->d_pieces, dp->d_tasks, dp->d_wide}, ipar, n, reads_a, aligned,
                    d_bufs, d_items, stream, true);
   if (st != COSTA_SUCCESS) return st;
-  if (ws->last_use) {
+  if (ws) {
     HIP_OR_FAIL(hipEventRecord(ws->last_use, stream));
     ws->last_stream = stream;
     ws->used = true;
@@ -539,7 +588,7 @@ extern "C" costa_status costa_set_workspace_limit(size_t bytes) {
 }
 
 // Host-only plan (no device): the workspace cap is the user limit, else unlimited.
-costa_status host_plan(costa_dtype dtype, int32_t n, const costa_transform_desc* desc, const int32_t* sigma,
+costa_status host_plan(Form form, costa_dtype dtype, int32_t n, const costa_transform_desc* desc, const int32_t* sigma,
                        const HostPlan*& out) {
   std::vector<ItemDesc> items;
   std::vector<int32_t> sig;
@@ -547,13 +596,13 @@ costa_status host_plan(costa_dtype dtype, int32_t n, const costa_transform_desc*
   if (st != COSTA_SUCCESS) return st;
   State& S = state();
   const int es = elem_size(dtype);
-  std::string key = plan_key(-1, es, items, sig, S.workspace_limit);
+  std::string key = plan_key(-1, form, es, items, sig, S.workspace_limit);
   auto it = S.host_plans.find(key);
   if (it == S.host_plans.end()) {
     if (S.host_plans.size() >= 32) S.host_plans.clear();
     std::unique_ptr<HostPlan> hp(new (std::nothrow) HostPlan());
     if (!hp) return fail(COSTA_ERROR_OUT_OF_MEMORY, "host allocation failed");
-    PlanConfig cfg = make_config(es);
+    PlanConfig cfg = make_config(es, form);
     size_t lim = S.workspace_limit;
     try {
       build_plan(items, sig, cfg, [lim](int64_t need) { return lim ? std::min<int64_t>(need, (int64_t)lim) : need; },
@@ -567,15 +616,14 @@ costa_status host_plan(costa_dtype dtype, int32_t n, const costa_transform_desc*
   return COSTA_SUCCESS;
 }
 
-extern "C" costa_status costa_plan_export(costa_dtype dtype, int32_t n, const costa_transform_desc* desc,
-                                          const int32_t* sigma, costa_piece_info* out, int64_t capacity,
-                                          int64_t* count) {
+static costa_status export_form(Form form, costa_dtype dtype, int32_t n, const costa_transform_desc* desc,
+                                const int32_t* sigma, costa_piece_info* out, int64_t capacity, int64_t* count) {
   return guarded([&]() -> costa_status {
     if (!count || capacity < 0 || (capacity > 0 && !out)) return fail(COSTA_ERROR_INVALID_VALUE, "bad output array");
     State& S = state();
     std::lock_guard<std::mutex> lock(S.mu);
     const HostPlan* hp = nullptr;
-    costa_status st = host_plan(dtype, n, desc, sigma, hp);
+    costa_status st = host_plan(form, dtype, n, desc, sigma, hp);
     if (st != COSTA_SUCCESS) return st;
     int64_t k = 0;
     int32_t launch = 0;
@@ -634,6 +682,18 @@ extern "C" costa_status costa_plan_export(costa_dtype dtype, int32_t n, const co
   });
 }
 
+extern "C" costa_status costa_plan_export(costa_dtype dtype, int32_t n, const costa_transform_desc* desc,
+                                          const int32_t* sigma, costa_piece_info* out, int64_t capacity,
+                                          int64_t* count) {
+  return export_form(FORM_MESSAGES, dtype, n, desc, sigma, out, capacity, count);
+}
+
+extern "C" costa_status costa_plan_export_direct(costa_dtype dtype, int32_t n, const costa_transform_desc* desc,
+                                                 const int32_t* sigma, costa_piece_info* out, int64_t capacity,
+                                                 int64_t* count) {
+  return export_form(FORM_DIRECT, dtype, n, desc, sigma, out, capacity, count);
+}
+
 extern "C" costa_status costa_plan_stats(costa_dtype dtype, int32_t n, const costa_transform_desc* desc,
                                          const int32_t* sigma, costa_stats* out) {
   return guarded([&]() -> costa_status {
@@ -641,7 +701,7 @@ extern "C" costa_status costa_plan_stats(costa_dtype dtype, int32_t n, const cos
     State& S = state();
     std::lock_guard<std::mutex> lock(S.mu);
     const HostPlan* hpp = nullptr;
-    costa_status st = host_plan(dtype, n, desc, sigma, hpp);
+    costa_status st = host_plan(FORM_MESSAGES, dtype, n, desc, sigma, hpp);
     if (st != COSTA_SUCCESS) return st;
     const HostPlan& hp = *hpp;
     const int es = elem_size(dtype);
@@ -833,12 +893,13 @@ static_assert(kNoallocTableBytes % 256 == 0 && kNoallocTableBytes < kNoallocByte
 // the address hipGetSymbolAddress returns on each device.
 static __device__ __align__(256) unsigned char scratch[kNoallocBytes];
 
-// A plan of the no-allocation path: planned for messages of at most
-// kNoallocMessageBytes per wave, with the offsets of its tables in the
-// scratch array.
+// A plan of the no-allocation path, with the offsets of its tables in the
+// scratch array; the message form is planned for messages of at most
+// kNoallocMessageBytes per wave.
 struct NoallocPlan {
   HostPlan host;
   uint64_t serial = 0;  // tells plans apart when one is rebuilt at a freed address
+  bool accepted = false;  // direct form: the message form's tables fit as well
   size_t off_tasks = 0, off_wide = 0, off_table = 0, end = 0;
 };
 
@@ -862,17 +923,18 @@ NoallocState& noalloc_state() {
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
-// Host plan of a no-allocation call (host memory only; no device call).
-costa_status noalloc_plan(costa_dtype dt, const std::vector<ItemDesc>& items, const std::vector<int32_t>& sig,
-                          NoallocPlan*& out) {
+// The cached plan of one form of a no-allocation call, built if need be (host
+// memory only; no device call).
+NoallocPlan& noalloc_form(Form form, costa_dtype dt, const std::vector<ItemDesc>& items,
+                          const std::vector<int32_t>& sig) {
   NoallocState& N = noalloc_state();
   const int es = elem_size(dt);
-  std::string key = plan_key(-1, es, items, sig, kNoallocMessageBytes);
+  std::string key = plan_key(-1, form, es, items, sig, kNoallocMessageBytes);
   auto it = N.plans.find(key);
   if (it == N.plans.end()) {
-    if (N.plans.size() >= 32) N.plans.clear();
+    if (N.plans.size() >= 64) N.plans.clear();
     std::unique_ptr<NoallocPlan> np(new NoallocPlan());
-    build_plan(items, sig, make_config(es),
+    build_plan(items, sig, make_config(es, form),
                [](int64_t need) { return std::min<int64_t>(need, (int64_t)kNoallocMessageBytes); }, np->host);
     const HostPlan& hp = np->host;
     const int32_t P = items.empty() ? 0 : items[0].A->nranks;
@@ -884,7 +946,41 @@ costa_status noalloc_plan(costa_dtype dt, const std::vector<ItemDesc>& items, co
     np->serial = N.next_serial++;
     it = N.plans.emplace(key, std::move(np)).first;
   }
-  NoallocPlan& np = *it->second;
+  return *it->second;
+}
+
+// Whether the message form's tables would fit the scratch array for sure,
+// from the direct plan's rectangles: at most two for each (a rectangle larger
+// than a wave's messages would be cut, so none may be), and for each of its
+// two launches tasks of at least 256 elements plus a rectangle's remainders
+// in both task tables.
+bool message_tables_fit(const NoallocPlan& dp, int es) {
+  size_t tasks = 0;
+  for (const Piece& p : dp.host.pieces) {
+    const int64_t ne = (int64_t)p.nx * p.ny;
+    if (ne * es + 255 > (int64_t)kNoallocMessageBytes) return false;
+    tasks += 2 * (size_t)(ne / kThreadsPerTask + 2);
+  }
+  const size_t table = dp.end - dp.off_table;
+  return 2 * dp.host.pieces.size() * sizeof(Piece) + 2 * tasks * sizeof(int32_t) + 3 * 256 + table <=
+         kNoallocTableBytes;
+}
+
+// The plan of a no-allocation call: the direct form where the caller's
+// buffers allow it (`direct`) and its tables fit.  What the entry point
+// accepts is decided by the message form's tables, which are planned only
+// where they might not fit.
+costa_status noalloc_plan(costa_dtype dt, const std::vector<ItemDesc>& items, const std::vector<int32_t>& sig,
+                          bool direct, NoallocPlan*& out) {
+  if (direct) {
+    NoallocPlan& dp = noalloc_form(FORM_DIRECT, dt, items, sig);
+    out = &dp;
+    if (dp.end <= kNoallocTableBytes && (dp.accepted || message_tables_fit(dp, elem_size(dt)))) {
+      dp.accepted = true;
+      return COSTA_SUCCESS;
+    }
+  }
+  NoallocPlan& np = noalloc_form(FORM_MESSAGES, dt, items, sig);
   if (np.end > kNoallocTableBytes)
     return fail(COSTA_ERROR_NOT_SUPPORTED, "the plan's tables need " + std::to_string(np.end) +
                                                " bytes; the no-allocation scratch holds " +
@@ -893,6 +989,15 @@ costa_status noalloc_plan(costa_dtype dt, const std::vector<ItemDesc>& items, co
   if ((size_t)np.host.workspace_bytes > kNoallocMessageBytes)
     return fail(COSTA_ERROR_NOT_SUPPORTED, "a wave's messages exceed the no-allocation scratch");
   out = &np;
+  if (!direct) return COSTA_SUCCESS;
+  // (planning the message form may have started the cache over)
+  NoallocPlan& dp = noalloc_form(FORM_DIRECT, dt, items, sig);
+  if (dp.end <= kNoallocTableBytes) {
+    dp.accepted = true;
+    out = &dp;
+  } else {
+    out = &noalloc_form(FORM_MESSAGES, dt, items, sig);
+  }
   return COSTA_SUCCESS;
 }
 
@@ -929,8 +1034,10 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
     if (total == 0) return COSTA_SUCCESS;
     // planning and the size checks come first: a request that does not fit
     // is refused before any device call
+    const int32_t P = items[0].A->nranks;
+    const bool direct = !a_overlaps_b(elem_size(dtype), n, desc, items, sig, P);
     NoallocPlan* np = nullptr;
-    st = noalloc_plan(dtype, items, sig, np);
+    st = noalloc_plan(dtype, items, sig, direct, np);
     if (st != COSTA_SUCCESS) return st;
     NoallocDevice* dev = nullptr;
     st = noalloc_device(dev);
@@ -953,7 +1060,6 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
                                    hipMemcpyHostToDevice, stream));
       dev->resident = np->serial;
     }
-    const int32_t P = items[0].A->nranks;
     std::vector<unsigned char> table;
     std::vector<char> reads_a;
     bool aligned = true;
@@ -978,7 +1084,7 @@ extern "C" costa_status costa_timing_enable(int on) {
     State& S = state();
     std::lock_guard<std::mutex> lock(S.mu);
     costa_status st = collect_timing(S);
-    S.timing = on != 0;
+    S.timing = on == COSTA_TIMING_AS_CALLED ? COSTA_TIMING_AS_CALLED : on != 0 ? COSTA_TIMING_MESSAGES : 0;
     S.totals = costa_timing{};
     // create the events up front (hipEventCreate can take tens of
     // microseconds; created lazily, they would land in the timed calls)
@@ -1034,7 +1140,7 @@ extern "C" costa_status costa_finalize(void) {
       for (auto& kv : S.event_pool)
         for (hipEvent_t e : kv.second) (void)hipEventDestroy(e);
       S.event_pool.clear();
-      S.timing = false;
+      S.timing = 0;
       S.totals = costa_timing{};
     }
     // outside the state lock: a ScaLAPACK-style call takes the layout cache's

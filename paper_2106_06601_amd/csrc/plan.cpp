@@ -784,6 +784,11 @@ void build_plan(const std::vector<ItemDesc>& items, const std::vector<int32_t>& 
       std::vector<Cand>().swap(rem[k]);
     }
   }
+  if (!cfg.messages) {
+    // the direct form: every block goes straight from B to A
+    local.insert(local.end(), remote.begin(), remote.end());
+    std::vector<Cand>().swap(remote);
+  }
   split_pieces(local, cfg.max_piece_elems);
   split_pieces(remote, cfg.max_piece_elems);
 

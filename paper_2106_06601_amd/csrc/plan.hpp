@@ -20,6 +20,8 @@ struct PlanConfig {
   int elem_size;           // bytes per element
   int64_t workspace_cap;   // max message bytes per wave (>= 1)
   int64_t max_piece_elems; // split rectangles larger than this (keeps per-rectangle indices in 32 bits)
+  bool messages;           // remote rectangles go through message buffers (pack, unpack-transform); else
+                           // every rectangle takes the direct path and the plan has no waves
 };
 
 struct HostPlan {
@@ -46,3 +48,10 @@ void build_plan(const std::vector<ItemDesc>& items, const std::vector<int32_t>& 
                 const std::function<int64_t(int64_t)>& choose_cap, HostPlan& out);
 
 }  // namespace costa
+
+// costa_plan_export() of the direct form: its rectangles, all DIRECT (the
+// transposed ones in a launch of their own, first, where both kinds occur).
+// For host-side checking of plans; not part of the public header.
+extern "C" costa_status costa_plan_export_direct(costa_dtype dtype, int32_t n, const costa_transform_desc* desc,
+                                                 const int32_t* sigma, costa_piece_info* out, int64_t capacity,
+                                                 int64_t* count);
