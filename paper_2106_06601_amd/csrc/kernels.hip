@@ -164,20 +164,49 @@ struct TypeTraits {
   static constexpr int TILE_PASSES = (tile_max_elems(ES) + kThreads - 1) / kThreads;  // elements per lane
 };
 
-// y = u / n and x = u - y*n from a float estimate of the quotient, corrected
-// to the exact one (u, n < 2^24: at most one step each way).
+// y = u / n and x = u - y*n for 0 <= u < 2^23, n >= 1 (n >= 2 from 2^22 on):
+// the estimate u * rcp(n) is off by at most 1.5 * 2^-23 of the quotient (rcp
+// to 1 ulp, one rounding of the product), less than one, so one step each way
+// makes it exact.  Selects, not loops: the corrections cost two instructions
+// each and no branch.
 __device__ __forceinline__ void divmod(int32_t u, int32_t n, int32_t& y, int32_t& x) {
-  y = (int32_t)((float)u * (1.0f / (float)n));
+  y = (int32_t)((float)u * __builtin_amdgcn_rcpf((float)n));
   x = u - y * n;
-  while (x < 0) {
-    --y;
-    x += n;
-  }
-  while (x >= n) {
-    ++y;
-    x -= n;
-  }
+  const bool under = x < 0;
+  y = under ? y - 1 : y;
+  x = under ? x + n : x;
+  const bool over = x >= n;
+  y = over ? y + 1 : y;
+  x = over ? x - n : x;
 }
+
+// A lane's way through the rows (`len` elements each) of a tile, kThreads
+// elements a step: the element's memory offset (row * ld + column) and its
+// LDS slot (row * ls + column * lc).  One division places the lane; every
+// step then adds the same two amounts, and one more where the step passes a
+// row's end (a step passes at most one: kThreads % len < len).
+struct TileWalk {
+  int32_t col, len, rem, lds, dlds, wlds;
+  int64_t off, doff, woff;
+  __device__ __forceinline__ TileWalk(int32_t tid, int32_t len_, int64_t ld, int32_t ls, int32_t lc) : len(len_) {
+    int32_t q, row;
+    divmod(kThreads, len, q, rem);
+    divmod(tid, len, row, col);
+    off = (int64_t)row * ld + col;
+    doff = (int64_t)q * ld + rem;
+    woff = ld - len;
+    lds = row * ls + col * lc;
+    dlds = q * ls + rem * lc;
+    wlds = ls - len * lc;
+  }
+  __device__ __forceinline__ void next() {
+    col += rem;
+    const bool wrap = col >= len;
+    col -= wrap ? len : 0;
+    off += doff + (wrap ? woff : 0);
+    lds += dlds + (wrap ? wlds : 0);
+  }
+};
 
 // Row walk: dst[y*dst_ld + x] = f(src[y*src_ld + x]).  The task starts at
 // unit u0 of rectangle pi (a unit is a 16-byte vector for PIECE_WIDE
@@ -529,67 +558,50 @@ __device__ __forceinline__ void move_tile(const Piece* __restrict__ pieces, int3
   const int32_t tid = threadIdx.x;
   const int32_t tx = tile_x_of(p.aux), ty = tile_y_of(p.aux);
   const int32_t stride = ty | 1;
-  const int32_t ntx = (p.nx + tx - 1) / tx;
-  const int32_t x0 = (c % ntx) * tx, y0 = (c / ntx) * ty;
+  int32_t rows, ntx, cy, cx;
+  divmod(p.nx + tx - 1, tx, ntx, rows);
+  divmod(c, ntx, cy, cx);
+  const int32_t x0 = cx * tx, y0 = cy * ty;
   const int32_t w = min(tx, p.nx - x0), h = min(ty, p.ny - y0);
   const int32_t n = w * h;
   const E* __restrict__ se = reinterpret_cast<const E*>(bufs[p.src_buf]) + p.src_off + (int64_t)x0 * p.src_ld + y0;
   E* __restrict__ de = reinterpret_cast<E*>(bufs[p.dst_buf]) + p.dst_off + (int64_t)y0 * p.dst_ld + x0;
   E v[NP];
+  int32_t slot[NP];
+  TileWalk in(tid, h, p.src_ld, stride, 1);
   // a tile as tall as its rectangle reads source lines no other tile reads
-  if (COSTA_NT_FULL_TILE_LOADS && h == p.ny) {
+  const bool full = COSTA_NT_FULL_TILE_LOADS && h == p.ny;
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      const int32_t i = k * kThreads + tid;
-      if (i < n) {
-        int32_t xl, yl;
-        divmod(i, h, xl, yl);
-        v[k] = load<true>(se + ((int64_t)xl * p.src_ld + yl));
-      }
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      const int32_t i = k * kThreads + tid;
-      if (i < n) {
-        int32_t xl, yl;
-        divmod(i, h, xl, yl);
-        v[k] = load<COSTA_NT_TILE_LOADS>(se + ((int64_t)xl * p.src_ld + yl));
-      }
-    }
+  for (int k = 0; k < NP; ++k) {
+    if (k * kThreads >= n) break;
+    slot[k] = in.lds;
+    if (k * kThreads + tid < n) v[k] = full ? load<true>(se + in.off) : load<COSTA_NT_TILE_LOADS>(se + in.off);
+    in.next();
   }
   E a[MODE == MODE_AXPBY ? NP : 1];
   if constexpr (MODE == MODE_AXPBY) {
+    TileWalk ain(tid, w, p.dst_ld, 1, stride);
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-      const int32_t i = k * kThreads + tid;
-      if (i < n) {
-        int32_t yl, xl;
-        divmod(i, w, yl, xl);
-        a[k] = load<COSTA_NT_TILE_ALOADS>(de + ((int64_t)yl * p.dst_ld + xl));
-      }
+      if (k * kThreads >= n) break;
+      if (k * kThreads + tid < n) a[k] = load<COSTA_NT_TILE_ALOADS>(de + ain.off);
+      ain.next();
     }
   }
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
-    const int32_t i = k * kThreads + tid;
-    if (i < n) {
-      int32_t xl, yl;
-      divmod(i, h, xl, yl);
-      lds[xl * stride + yl] = v[k];
-    }
+    if (k * kThreads >= n) break;
+    if (k * kThreads + tid < n) lds[slot[k]] = v[k];
   }
   __syncthreads();
+  TileWalk out(tid, w, p.dst_ld, 1, stride);
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
-    const int32_t i = k * kThreads + tid;
-    if (i < n) {
-      int32_t yl, xl;
-      divmod(i, w, yl, xl);
-      store(de + ((int64_t)yl * p.dst_ld + xl),
-            combine<S, TT::NS, CPLX, MODE, CONJ>(lds[xl * stride + yl], a[MODE == MODE_AXPBY ? k : 0], ar, ai, br,
-                                                 bi));
-    }
+    if (k * kThreads >= n) break;
+    if (k * kThreads + tid < n)
+      store(de + out.off,
+            combine<S, TT::NS, CPLX, MODE, CONJ>(lds[out.lds], a[MODE == MODE_AXPBY ? k : 0], ar, ai, br, bi));
+    out.next();
   }
 }
 
@@ -810,17 +822,15 @@ hipError_t go(const Launch& l) {
 
 template <typename S, bool CPLX, int KIND, bool HAS_T>
 hipError_t go_mode(const Launch& l, int mode, int conj) {
-  // fixed-mode kernels for the element types of the hot workloads; the rest
-  // read the mode per rectangle
-  constexpr bool SPECIALISE = sizeof(S) == 8;
-  if constexpr (SPECIALISE) {
-    if (mode == MODE_COPY) return conj ? go<S, CPLX, KIND, MODE_COPY, CPLX, HAS_T>(l)
-                                       : go<S, CPLX, KIND, MODE_COPY, false, HAS_T>(l);
-    if (mode == MODE_SCALE) return conj ? go<S, CPLX, KIND, MODE_SCALE, CPLX, HAS_T>(l)
-                                        : go<S, CPLX, KIND, MODE_SCALE, false, HAS_T>(l);
-    if (mode == MODE_AXPBY) return conj ? go<S, CPLX, KIND, MODE_AXPBY, CPLX, HAS_T>(l)
-                                        : go<S, CPLX, KIND, MODE_AXPBY, false, HAS_T>(l);
-  }
+  // one mode for the whole call: its own kernel (the per-pair kernel holds
+  // the registers of every mode: float tiles 86 against 50, five waves per
+  // SIMD against eight)
+  if (mode == MODE_COPY) return conj ? go<S, CPLX, KIND, MODE_COPY, CPLX, HAS_T>(l)
+                                     : go<S, CPLX, KIND, MODE_COPY, false, HAS_T>(l);
+  if (mode == MODE_SCALE) return conj ? go<S, CPLX, KIND, MODE_SCALE, CPLX, HAS_T>(l)
+                                      : go<S, CPLX, KIND, MODE_SCALE, false, HAS_T>(l);
+  if (mode == MODE_AXPBY) return conj ? go<S, CPLX, KIND, MODE_AXPBY, CPLX, HAS_T>(l)
+                                      : go<S, CPLX, KIND, MODE_AXPBY, false, HAS_T>(l);
   return go<S, CPLX, KIND, MODE_ANY, false, HAS_T>(l);
 }
 
