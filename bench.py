@@ -293,7 +293,8 @@ PMC_STALLS = ["SQ_WAVES SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_L
               "TA_BUSY_avr TA_ADDR_STALLED_BY_TC_CYCLES_sum GRBM_GUI_ACTIVE"]
 _MODES = {0: "copy", 1: "scale", 2: "axpby", 3: "per pair"}
 _TEMPLATE_NOTE = ("Kernel template arguments: <scalar, complex, kind (0 pack, 1 unpack-transform, 2 direct), "
-                  "mode (0 copy, 1 scale, 2 axpby, 3 per pair), conjugate, LDS tiles>.")
+                  "mode (0 copy, 1 scale, 2 axpby, 3 per pair), conjugate>; costa_tiles also has the lanes of a "
+                  "workgroup.")
 
 
 def _bench_args(name: str) -> str:
@@ -346,11 +347,11 @@ def _short_name(name: str) -> str:
 
 def _mover_args(n: str):
     import re
-    m = re.match(r"costa_mover(?:_lds)?<(\w+), (\w+), (\d), (\d), (\w+), (\w+)>", n)
+    m = re.match(r"costa_(mover|tiles)<(\w+), (\w+), (\d), (\d), (\w+)", n)
     if not m:
         return None
-    return {"kind": int(m.group(3)), "mode": int(m.group(4)), "conj": m.group(5) == "true",
-            "tiles": m.group(6) == "true"}
+    return {"kind": int(m.group(4)), "mode": int(m.group(5)), "conj": m.group(6) == "true",
+            "tiles": m.group(1) == "tiles"}
 
 
 def _role(n: str) -> str:

@@ -288,10 +288,10 @@ costa_status run_range(State& S, MoverKind kind, costa_dtype dt, const DeviceTab
     }
     HIP_OR_FAIL(hipEventRecord(e0, stream));
   }
-  LaunchSpec spec{mode, conj, lr.has_transpose};
+  LaunchSpec spec{mode, conj, lr.tile_lanes};
   HIP_OR_FAIL(launch_mover(kind, dt, spec, dt_.pieces, dt_.tasks + lr.task_begin, lr.ntasks,
                            lr.nwide ? dt_.wide + lr.wide_begin : nullptr, lr.nwide, d_bufs, d_items, allow_wide,
-                           lr.xcd_ranges, stream));
+                           lr.xcd_run, stream));
   if (e1) {
     HIP_OR_FAIL(hipEventRecord(e1, stream));
     costa_kernel_kind kk = kind == KIND_PACK ? COSTA_KERNEL_PACK

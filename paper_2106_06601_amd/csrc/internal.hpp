@@ -212,65 +212,60 @@ inline int64_t stack_tasks(int64_t hu, int64_t ny) {
 // Elements per 16-byte unit of a PIECE_WIDE rectangle.
 constexpr int32_t wide_elems(int32_t es) { return es >= 16 ? 1 : 16 / es; }
 
-// LDS tiles of transposed rectangles.  A tile is at most tile_max_x(es)
-// wide; its rows (one per x) take tile_y | 1 elements in LDS -- an odd
-// stride, so that lanes reading one LDS row element each (consecutive x) hit
-// distinct banks -- and all of them fit the tile's LDS array of
-// tile_lds_elems(es) elements.  Small rectangles are one tile; larger ones
-// are cut into tiles of equal width (at most tile_max_x) and equal height.
-// When the rectangle's source columns start on 128-byte lines the height is
-// what tile_budget(es) elements allow (for the usual shapes a whole number of
-// lines per column, so no tile shares a line with the one below it, and the
-// lanes storing a column to LDS do not straddle two columns).  Otherwise the
-// height is odd and as large as the LDS array allows: the rows then need no
-// padding, so the lanes storing a tile's columns one after another write
-// consecutive LDS addresses (padded rows would make each group of lanes that
-// crosses a column end hit one bank twice).
+// LDS tiles of transposed rectangles, moved by workgroups of `lanes` lanes
+// (the tile lanes of a launch: kThreadsPerTask, or kSmallTileLanes in launches
+// of small rectangles).  A tile is at most tile_max_x wide; its rows (one per
+// x) take tile_y | 1 elements in LDS -- an odd stride, so that lanes reading
+// one LDS row element each (consecutive x) hit distinct banks -- and all of
+// them fit the tile's LDS array of tile_lds_elems elements.  Small rectangles
+// are one tile; larger ones are cut into tiles of equal width (at most
+// tile_max_x) and equal height, as tall as tile_budget elements allow (for
+// the usual shapes a whole number of 128-byte lines per source column, so no
+// tile shares a line with the one below it).
 #ifndef COSTA_TILE_BUDGET16
 #define COSTA_TILE_BUDGET16 3072  // three workgroups per CU (4096: two, -1 to -9%; 2048: four, shorter tiles)
 #endif
 #ifndef COSTA_TILE_MAXX16
 #define COSTA_TILE_MAXX16 256
 #endif
-#ifndef COSTA_ODD_TILES
-#define COSTA_ODD_TILES 0  // 1: cut tiles of misaligned columns with an odd height that fills the LDS array
-#endif
-constexpr int32_t tile_budget(int32_t es) { return es >= 16 ? COSTA_TILE_BUDGET16 : es == 8 ? 2048 : 4096; }
-constexpr int32_t tile_max_x(int32_t es) { return es >= 16 ? COSTA_TILE_MAXX16 : 128; }
-constexpr int32_t tile_lds_elems(int32_t es) { return tile_budget(es) + tile_max_x(es); }
-// Elements of the largest tile (what a workgroup's lanes must cover).
-constexpr int32_t tile_max_elems(int32_t es) { return COSTA_ODD_TILES ? tile_lds_elems(es) : tile_budget(es); }
+// Lanes and tile elements of launches of small rectangles: one wave per tile,
+// so that a CU holds 16 to 32 tiles in flight instead of eight (a 256-lane
+// workgroup of a 144-element tile leaves half its lanes idle and all of them
+// waiting for one round of loads).  The elements are 12 a lane for 8-byte
+// types (measured at 16: pdtran's 655-element tiles -4%; 8 and 16 a lane for
+// complex128 and float).
+constexpr int32_t kSmallTileLanes = 64;
+constexpr int32_t tile_budget(int32_t es, int32_t lanes) {
+  if (lanes == kSmallTileLanes) return es >= 16 ? 512 : es == 8 ? 768 : 1024;
+  return es >= 16 ? COSTA_TILE_BUDGET16 : es == 8 ? 2048 : 4096;
+}
+constexpr int32_t tile_max_x(int32_t es, int32_t lanes) {
+  return lanes == kSmallTileLanes ? 64 : es >= 16 ? COSTA_TILE_MAXX16 : 128;
+}
+constexpr int32_t tile_lds_elems(int32_t es, int32_t lanes) { return tile_budget(es, lanes) + tile_max_x(es, lanes); }
+// Mean elements of a launch's (256-lane) tiles up to which it takes small
+// ones.  Measured on MI355X, one wave against four per tile: 144 elements
+// -35% (8-byte copy 300 -> 197 us), float accumulate 824 -> 336; 576 elements
+// -10% (8-byte), -22% (float), -26% (complex128); 1024 elements: 8-byte +5%,
+// float -4 to -10%, complex128 -10%; 2304: float -15%, complex128 even; 3500
+// elements slower in every type (8-byte +11%, float +15%).
+constexpr int32_t small_tile_mean(int32_t es) { return es >= 16 ? 1100 : es == 8 ? 700 : 2400; }
 constexpr int32_t tile_pack(int32_t tx, int32_t ty) { return tx | ty << 16; }
 constexpr int32_t tile_x_of(int32_t t) { return t & 0xffff; }
 constexpr int32_t tile_y_of(int32_t t) { return t >> 16; }
-// aligned_cols: the source columns (runs along y) start on 128-byte lines.
-inline void choose_tile(int32_t es, int32_t nx, int32_t ny, bool aligned_cols, int32_t& tx, int32_t& ty) {
-  const int32_t maxx = tile_max_x(es);
-  const bool odd = COSTA_ODD_TILES && !aligned_cols;
-  const int32_t cap = tile_lds_elems(es), budget = tile_budget(es);
-  if (nx <= maxx && (odd ? (int64_t)nx * (ny | 1) <= cap : (int64_t)nx * ny <= budget)) {
+inline void choose_tile(int32_t es, int32_t lanes, int32_t nx, int32_t ny, int32_t& tx, int32_t& ty) {
+  const int32_t maxx = tile_max_x(es, lanes), budget = tile_budget(es, lanes);
+  if (nx <= maxx && (int64_t)nx * ny <= budget) {
     tx = nx;
     ty = ny;
     return;
   }
   const int32_t ntx = (nx + maxx - 1) / maxx;
   tx = (nx + ntx - 1) / ntx;
-  if (!odd) {
-    ty = budget / tx;
-    if (ty > ny) ty = ny;
-    const int32_t nty = (ny + ty - 1) / ty;
-    ty = (ny + nty - 1) / nty;
-    return;
-  }
-  int32_t tymax = cap / tx;  // >= 1: tx <= maxx < cap
-  if (tymax > 1 && tymax % 2 == 0) --tymax;  // odd: rows without padding
-  if (ny <= tymax) {
-    ty = ny;  // one tile row: (ny | 1) <= tymax since tymax is odd (or 1)
-    return;
-  }
-  const int32_t nty = (ny + tymax - 1) / tymax;
+  ty = budget / tx;
+  if (ty > ny) ty = ny;
+  const int32_t nty = (ny + ty - 1) / ty;
   ty = (ny + nty - 1) / nty;
-  if (ty % 2 == 0 && ty < tymax) ++ty;  // keeps at most nty tiles, the last one shorter
 }
 
 // Per-pair parameters of a call, read by the kernels.
@@ -294,8 +289,8 @@ struct LaunchRange {
   int64_t task_begin = 0, ntasks = 0;
   int64_t wide_begin = 0, nwide = 0;  // wide task table (launches without tiles; 0 tasks otherwise)
   int64_t elems = 0;
-  bool has_transpose = false;
-  int32_t xcd_ranges = 0;  // 1: each XCD takes one contiguous range of the launch's tasks
+  int32_t tile_lanes = 0;  // lanes a workgroup of a launch of tiles has; 0: a launch of row walks
+  int32_t xcd_run = 0;  // consecutive tasks each XCD takes at a time (see launch_mover)
   std::vector<int64_t> item_elems;  // elements of each pair in this launch
 };
 
@@ -310,22 +305,23 @@ struct Wave {
 // ---- kernels (kernels.hip) -------------------------------------------------
 enum MoverKind : int32_t { KIND_PACK = 0, KIND_UNPACK = 1, KIND_DIRECT = 2 };
 // What one launch needs: the pairs' common arithmetic mode and conjugation
-// (mode -1: the pairs differ, read per rectangle) and whether any rectangle
-// of the launch is transposed.
+// (mode -1: the pairs differ, read per rectangle) and the lanes a workgroup
+// has when its rectangles are LDS tiles (0: row walks).
 struct LaunchSpec {
   int32_t mode;
   int32_t conj;
-  bool has_transpose;
+  int32_t tile_lanes;
 };
 // pieces: the plan's rectangles (global indices); tasks: the launch's
 // ntasks entries, wide: its wide task table (nwide entries, 0 in launches
 // with tiles).
-// xcd_ranges: 0 runs task b in workgroup b (workgroups are dispatched
-// round-robin over the 8 XCDs); 1 hands each XCD one contiguous range of the
-// tasks of each launch slice.
+// xcd_run: 0 runs task b in workgroup b (workgroups are dispatched
+// round-robin over the 8 XCDs); k > 0 hands the XCDs runs of k consecutive
+// tasks in turn; -1 hands each XCD one contiguous range of the tasks of each
+// launch slice.
 hipError_t launch_mover(MoverKind kind, costa_dtype dtype, const LaunchSpec& spec, const Piece* pieces,
                         const int32_t* tasks, int64_t ntasks, const int32_t* wide, int64_t nwide, void* const* bufs,
-                        const ItemParam* items, int32_t allow_wide, int32_t xcd_ranges, hipStream_t stream);
+                        const ItemParam* items, int32_t allow_wide, int32_t xcd_run, hipStream_t stream);
 
 struct VolumeArgs {
   const Interval* rows;

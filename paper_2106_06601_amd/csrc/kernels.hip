@@ -13,6 +13,8 @@
 // tasks are all alike may hand each XCD (one L2) a contiguous range of them.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.hpp"
 
 // Products and sums are rounded one by one, never fused into an FMA, so the
@@ -29,36 +31,40 @@ namespace {
 #ifndef COSTA_NT_LOADS_MAX_ES
 #define COSTA_NT_LOADS_MAX_ES 8  // ...for element sizes up to this (measured: helps fp64, hurts complex128)
 #endif
-#ifndef COSTA_NT_TILE_LOADS
-#define COSTA_NT_TILE_LOADS 0  // tile loads: lines may serve two neighbouring tiles
-#endif
-#ifndef COSTA_NT_FULL_TILE_LOADS
-#define COSTA_NT_FULL_TILE_LOADS 1  // ...except in a tile as tall as its rectangle (pdtran +2.7% per step;
-#endif                              // all tile loads NT: the complex case -19%)
 #ifndef COSTA_NT_STORES
 #define COSTA_NT_STORES 1
 #endif
 #ifndef COSTA_NT_ALOADS
 #define COSTA_NT_ALOADS 0  // loads of A in row walks (measured: 1 makes the scaled transpose's unpack 29% slower)
 #endif
-// Loads of A in LDS tiles.  Measured with 1: the tiles' unpack 1-2% slower,
-// but the pack of the next call faster (pztranc's +7%, the tall-skinny
-// batch's +1 to +3%): whole steps +1.2 to +1.4%.
-#ifndef COSTA_NT_TILE_ALOADS
-#define COSTA_NT_TILE_ALOADS 1
-#endif
+// Runs (bytes) from which a tile's loads are non-temporal although its runs
+// end inside 128-byte lines that a neighbouring tile reads too; below it such
+// tiles use plain loads, and the neighbour finds the line in L2 or in the
+// Infinity Cache.  Measured on MI355X, plain against non-temporal:
+//   source columns of 12 floats 251 against 412 us, 22 floats 236 - 318, 22
+//   doubles 173 - 206, 59 floats 141 - 150, 32 doubles (pdtran) 830 - 858, 59
+//   doubles 131 - 129; whole lines (32 and 48 doubles) 121 - 111;
+//   rows of A (in launches that hand an XCD runs of tiles) 22 floats
+//   247 - 277, 22 doubles 221 - 231, 59 doubles 199 - 181; whole lines
+//   189 - 159.
+constexpr int kShortTileColumn = 384, kShortTileRow = 256;
 
 constexpr int kThreads = kThreadsPerTask;
 
 // The task of workgroup b of n.  Workgroups are dispatched round-robin over
-// the 8 XCDs (b % 8 is b's XCD).  ranges 0: task b.  ranges 1: XCD x takes
-// the x-th of 8 contiguous ranges of tasks, workgroup b the (b/8)-th task of
-// its XCD's range.
-__device__ __forceinline__ int32_t xcd_order(int32_t b, int32_t n, int32_t ranges) {
+// the 8 XCDs (b % 8 is b's XCD).  run 0: task b.  run -1: XCD x takes the
+// x-th of 8 contiguous ranges of tasks, workgroup b the (b/8)-th task of its
+// XCD's range.  run k > 0: the XCDs take runs of k consecutive tasks in turn
+// (tasks past the last whole round of runs: task b).
+__device__ __forceinline__ int32_t xcd_order(int32_t b, int32_t n, int32_t run) {
   constexpr int32_t X = 8;
-  if (!ranges) return b;
-  const int32_t q = n / X, r = n % X;
+  if (run == 0) return b;
   const int32_t xcd = b % X, idx = b / X;
+  if (run > 0) {
+    const int32_t turn = idx / run;
+    return (turn + 1) * X * run > n ? b : (turn * X + xcd) * run + idx - turn * run;
+  }
+  const int32_t q = n / X, r = n % X;
   const int32_t start = xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q;
   return start + idx;
 }
@@ -160,8 +166,6 @@ struct TypeTraits {
   static constexpr int ES = (int)sizeof(S) * NS;  // bytes per element
   static constexpr int WIDE_NEL = wide_elems(ES); // elements per 16-byte unit
   static constexpr bool NT_WALK = COSTA_NT_LOADS && ES <= COSTA_NT_LOADS_MAX_ES;
-  static constexpr int LDS_ELEMS = tile_lds_elems(ES);
-  static constexpr int TILE_PASSES = (tile_max_elems(ES) + kThreads - 1) / kThreads;  // elements per lane
 };
 
 // y = u / n and x = u - y*n for 0 <= u < 2^23, n >= 1 (n >= 2 from 2^22 on):
@@ -180,17 +184,18 @@ __device__ __forceinline__ void divmod(int32_t u, int32_t n, int32_t& y, int32_t
   x = over ? x - n : x;
 }
 
-// A lane's way through the rows (`len` elements each) of a tile, kThreads
+// A lane's way through the rows (`len` elements each) of a tile, T
 // elements a step: the element's memory offset (row * ld + column) and its
 // LDS slot (row * ls + column * lc).  One division places the lane; every
 // step then adds the same two amounts, and one more where the step passes a
-// row's end (a step passes at most one: kThreads % len < len).
+// row's end (a step passes at most one: T % len < len).
+template <int T>
 struct TileWalk {
   int32_t col, len, rem, lds, dlds, wlds;
   int64_t off, doff, woff;
   __device__ __forceinline__ TileWalk(int32_t tid, int32_t len_, int64_t ld, int32_t ls, int32_t lc) : len(len_) {
     int32_t q, row;
-    divmod(kThreads, len, q, rem);
+    divmod(T, len, q, rem);
     divmod(tid, len, row, col);
     off = (int64_t)row * ld + col;
     doff = (int64_t)q * ld + rem;
@@ -547,13 +552,13 @@ __device__ __forceinline__ void move_stack(const Piece* __restrict__ pieces, int
 // loads issued between the stores could not be moved ahead of them (the
 // compiler cannot tell that they touch other elements) and would each wait
 // for a full memory round trip.
-template <typename S, bool CPLX, int MODE, bool CONJ>
+template <typename S, bool CPLX, int MODE, bool CONJ, int T>
 __device__ __forceinline__ void move_tile(const Piece* __restrict__ pieces, int32_t pi, int32_t c,
-                                          void* const* __restrict__ bufs, Vec<S, CPLX ? 2 : 1>* lds, S ar, S ai,
-                                          S br, S bi) {
+                                          void* const* __restrict__ bufs, int32_t xcd_run,
+                                          Vec<S, CPLX ? 2 : 1>* lds, S ar, S ai, S br, S bi) {
   using TT = TypeTraits<S, CPLX>;
   using E = Vec<S, TT::NS>;
-  constexpr int NP = TT::TILE_PASSES;
+  constexpr int NP = (tile_budget(TT::ES, T) + T - 1) / T;  // elements per lane
   const Piece& p = pieces[pi];
   const int32_t tid = threadIdx.x;
   const int32_t tx = tile_x_of(p.aux), ty = tile_y_of(p.aux);
@@ -568,48 +573,62 @@ __device__ __forceinline__ void move_tile(const Piece* __restrict__ pieces, int3
   E* __restrict__ de = reinterpret_cast<E*>(bufs[p.dst_buf]) + p.dst_off + (int64_t)y0 * p.dst_ld + x0;
   E v[NP];
   int32_t slot[NP];
-  TileWalk in(tid, h, p.src_ld, stride, 1);
-  // a tile as tall as its rectangle reads source lines no other tile reads
-  const bool full = COSTA_NT_FULL_TILE_LOADS && h == p.ny;
-#pragma unroll
-  for (int k = 0; k < NP; ++k) {
-    if (k * kThreads >= n) break;
-    slot[k] = in.lds;
-    if (k * kThreads + tid < n) v[k] = full ? load<true>(se + in.off) : load<COSTA_NT_TILE_LOADS>(se + in.off);
-    in.next();
-  }
-  E a[MODE == MODE_AXPBY ? NP : 1];
-  if constexpr (MODE == MODE_AXPBY) {
-    TileWalk ain(tid, w, p.dst_ld, 1, stride);
+  // (one loop per cache policy, kept apart by an empty asm: the compiler
+  // merges two loads of one address into one without the non-temporal hint)
+  auto load_source = [&](auto nt) {
+    if constexpr (decltype(nt)::value) asm volatile("");
+    TileWalk<T> in(tid, h, p.src_ld, stride, 1);
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-      if (k * kThreads >= n) break;
-      if (k * kThreads + tid < n) a[k] = load<COSTA_NT_TILE_ALOADS>(de + ain.off);
+      if (k * T >= n) break;
+      slot[k] = in.lds;
+      if (k * T + tid < n) v[k] = load<decltype(nt)::value>(se + in.off);
+      in.next();
+    }
+  };
+  // a tile as tall as its rectangle shares no source line with another one
+  // when its columns start and end on lines, and few when they are long
+  constexpr int32_t L = 128 / TT::ES;  // elements of a line
+  const bool own_lines = h == p.ny && (h * TT::ES >= kShortTileColumn || (p.src_off | p.src_ld | h) % L == 0);
+  if (own_lines) load_source(std::true_type{});
+  else load_source(std::false_type{});
+  E a[MODE == MODE_AXPBY ? NP : 1];
+  auto load_a = [&](auto nt) {
+    if constexpr (decltype(nt)::value) asm volatile("");
+    TileWalk<T> ain(tid, w, p.dst_ld, 1, stride);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      if (k * T >= n) break;
+      if (k * T + tid < n) a[k] = load<decltype(nt)::value>(de + ain.off);
       ain.next();
     }
+  };
+  if constexpr (MODE == MODE_AXPBY) {
+    if (xcd_run > 0 && w * TT::ES < kShortTileRow) load_a(std::false_type{});
+    else load_a(std::true_type{});
   }
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
-    if (k * kThreads >= n) break;
-    if (k * kThreads + tid < n) lds[slot[k]] = v[k];
+    if (k * T >= n) break;
+    if (k * T + tid < n) lds[slot[k]] = v[k];
   }
   __syncthreads();
-  TileWalk out(tid, w, p.dst_ld, 1, stride);
+  TileWalk<T> out(tid, w, p.dst_ld, 1, stride);
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
-    if (k * kThreads >= n) break;
-    if (k * kThreads + tid < n)
+    if (k * T >= n) break;
+    if (k * T + tid < n)
       store(de + out.off,
             combine<S, TT::NS, CPLX, MODE, CONJ>(lds[out.lds], a[MODE == MODE_AXPBY ? k : 0], ar, ai, br, bi));
     out.next();
   }
 }
 
-// The work of one workgroup for a fixed arithmetic mode.
-template <typename S, bool CPLX, int MODE, bool CONJ, bool HAS_T, int UL>
-__device__ __forceinline__ void move_task(const Piece* __restrict__ pieces, int32_t pi, int32_t flags, int32_t c,
+// The row walk of one workgroup for a fixed arithmetic mode.
+template <typename S, bool CPLX, int MODE, bool CONJ, int UL>
+__device__ __forceinline__ void walk_task(const Piece* __restrict__ pieces, int32_t pi, int32_t c,
                                           void* const* __restrict__ bufs, const ItemParam* __restrict__ ip,
-                                          int32_t allow_wide, Vec<S, CPLX ? 2 : 1>* lds) {
+                                          int32_t allow_wide) {
   S ar = S(0), ai = S(0), br = S(0), bi = S(0);
   if constexpr (MODE != MODE_COPY) {
     ar = (S)ip->alpha[0];
@@ -617,14 +636,9 @@ __device__ __forceinline__ void move_task(const Piece* __restrict__ pieces, int3
     br = (S)ip->beta[0];
     bi = (S)ip->beta[1];
   }
-  if constexpr (HAS_T) {
-    if (flags & PIECE_TRANSPOSE) {
-      move_tile<S, CPLX, MODE, CONJ>(pieces, pi, c, bufs, lds, ar, ai, br, bi);
-      return;
-    }
-  } else if constexpr (MODE != MODE_AXPBY) {
+  if constexpr (MODE != MODE_AXPBY) {
     // stacks outside the pack hold only rectangles of pairs that do not read A
-    if (flags & PIECE_STACK) {
+    if (pieces[pi].flags & PIECE_STACK) {
       move_stack<S, CPLX, MODE, CONJ>(pieces, pi, c, bufs, allow_wide, ar, ai, br, bi);
       return;
     }
@@ -635,27 +649,63 @@ __device__ __forceinline__ void move_task(const Piece* __restrict__ pieces, int3
     move_walk<S, CPLX, MODE, CONJ, UL>(pieces, pi, c * (UL * kThreads), bufs, allow_wide, ar, ai, br, bi);
 }
 
-constexpr int MODE_ANY = 3;
+// The LDS tile of one workgroup for a fixed arithmetic mode.
+template <typename S, bool CPLX, int MODE, bool CONJ, int T>
+__device__ __forceinline__ void tile_task(const Piece* __restrict__ pieces, int32_t pi, int32_t c,
+                                          void* const* __restrict__ bufs, const ItemParam* __restrict__ ip,
+                                          int32_t xcd_run, Vec<S, CPLX ? 2 : 1>* lds) {
+  S ar = S(0), ai = S(0), br = S(0), bi = S(0);
+  if constexpr (MODE != MODE_COPY) {
+    ar = (S)ip->alpha[0];
+    ai = (S)ip->alpha[1];
+    br = (S)ip->beta[0];
+    bi = (S)ip->beta[1];
+  }
+  move_tile<S, CPLX, MODE, CONJ, T>(pieces, pi, c, bufs, xcd_run, lds, ar, ai, br, bi);
+}
 
-// One launch slice: workgroup b moves task task_off + xcd_order(b) of the
-// launch's task table.
-//   KIND: pack (bitwise copy into message buffers, never transposed),
-//         unpack-transform, or direct.
-//   MODE: the arithmetic of every pair of the call, or MODE_ANY to read it
-//         per workgroup (batches that mix modes; a workgroup's rectangles
-//         belong to one pair); CONJ likewise.
-//   HAS_T: whether the launch contains transposed rectangles (LDS tiles).
-//   UL: units per lane of its row walks; with UL = 2 the table is the
-//       launch's wide task table, whose first task of a rectangle is in aux.
-template <typename S, bool CPLX, int KIND, int MODE, bool CONJ, bool HAS_T, int UL>
-__device__ __forceinline__ void mover_body(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks,
-                                           int32_t task_off, void* const* __restrict__ bufs,
-                                           const ItemParam* __restrict__ items, int32_t allow_wide,
-                                           int32_t ranges) {
+// MODE of a kernel that reads the mode and the conjugation of its rectangle's
+// pair (batches that mix them; a workgroup's rectangles belong to one pair).
+constexpr int MODE_ANY = 3;
+#define COSTA_BY_MODE(TASK)                                  \
+  do {                                                       \
+    const bool conj = CPLX && ip->conj;                      \
+    if (ip->mode == MODE_COPY) {                             \
+      if (conj) TASK(MODE_COPY, CPLX);                       \
+      else TASK(MODE_COPY, false);                           \
+    } else if (ip->mode == MODE_SCALE) {                     \
+      if (conj) TASK(MODE_SCALE, CPLX);                      \
+      else TASK(MODE_SCALE, false);                          \
+    } else {                                                 \
+      if (conj) TASK(MODE_AXPBY, CPLX);                      \
+      else TASK(MODE_AXPBY, false);                          \
+    }                                                        \
+  } while (0)
+
+// Units per lane of a launch of row walks: two (the wide task table) in
+// launches that copy -- the pack, and unpack/direct launches with alpha = 1,
+// beta = 0 -- one otherwise.  Measured on MI355X: two units per lane +2 to
+// +11% on copies; on an axpby walk of short misaligned rows -19%.
+template <int KIND, int MODE>
+constexpr int units_per_lane() {
+  return KIND == KIND_PACK || MODE == MODE_COPY ? COSTA_COPY_UNITS : 1;
+}
+
+// One launch slice of row walks: workgroup b moves task task_off +
+// xcd_order(b) of the launch's task table.
+//   KIND: pack (bitwise copy into message buffers), unpack-transform, or
+//         direct.
+//   MODE, CONJ: the arithmetic of every pair of the call, or MODE_ANY.
+// With two units per lane the table is the launch's wide task table, whose
+// first task of a rectangle is in aux.
+template <typename S, bool CPLX, int KIND, int MODE, bool CONJ>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8)))
+costa_mover(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks, int32_t task_off,
+            void* const* __restrict__ bufs, const ItemParam* __restrict__ items, int32_t allow_wide,
+            int32_t xcd_run) {
   using TT = TypeTraits<S, CPLX>;
-  using E = Vec<S, TT::NS>;
-  __shared__ E lds[HAS_T ? TT::LDS_ELEMS : 1];
-  const int32_t b = task_off + xcd_order((int32_t)blockIdx.x, (int32_t)gridDim.x, ranges);
+  constexpr int UL = units_per_lane<KIND, MODE>();
+  const int32_t b = task_off + xcd_order((int32_t)blockIdx.x, (int32_t)gridDim.x, xcd_run);
   const int32_t pi = tasks[b];
   const int32_t c = b - (UL == 1 ? pieces[pi].task0 : pieces[pi].aux);
   if constexpr (KIND == KIND_PACK) {
@@ -669,61 +719,36 @@ __device__ __forceinline__ void mover_body(const Piece* __restrict__ pieces, con
       move_walk<S, CPLX, MODE_COPY, false, UL>(pieces, pi, c * (UL * kThreads), bufs, allow_wide, S(0), S(0), S(0),
                                                S(0));
   } else {
-    const int32_t flags = pieces[pi].flags;
     const ItemParam* ip = items + pieces[pi].item;
     if constexpr (MODE != MODE_ANY) {
-      move_task<S, CPLX, MODE, CONJ, HAS_T, UL>(pieces, pi, flags, c, bufs, ip, allow_wide, lds);
+      walk_task<S, CPLX, MODE, CONJ, UL>(pieces, pi, c, bufs, ip, allow_wide);
     } else {
-      const bool conj = CPLX && ip->conj;
-      const int32_t mode = ip->mode;
-#define COSTA_TASK(M, CJ) move_task<S, CPLX, M, CJ, HAS_T, UL>(pieces, pi, flags, c, bufs, ip, allow_wide, lds)
-      if (mode == MODE_COPY) {
-        if (conj) COSTA_TASK(MODE_COPY, CPLX);
-        else COSTA_TASK(MODE_COPY, false);
-      } else if (mode == MODE_SCALE) {
-        if (conj) COSTA_TASK(MODE_SCALE, CPLX);
-        else COSTA_TASK(MODE_SCALE, false);
-      } else {
-        if (conj) COSTA_TASK(MODE_AXPBY, CPLX);
-        else COSTA_TASK(MODE_AXPBY, false);
-      }
+#define COSTA_TASK(M, CJ) walk_task<S, CPLX, M, CJ, UL>(pieces, pi, c, bufs, ip, allow_wide)
+      COSTA_BY_MODE(COSTA_TASK);
 #undef COSTA_TASK
     }
   }
 }
 
-// Tile sizes that leave room for at least four workgroups per CU (160 KiB of
-// LDS) are compiled for at least four waves per SIMD; larger tiles (the big
-// complex128 tile) for two.
-template <typename S, bool CPLX, bool HAS_T>
-constexpr bool big_lds() {
-  return HAS_T && TypeTraits<S, CPLX>::LDS_ELEMS * TypeTraits<S, CPLX>::ES > 40 * 1024;
-}
-
-// Units per lane of a launch: two (the wide task table) in launches of row
-// walks that copy -- the pack, and unpack/direct launches with alpha = 1,
-// beta = 0 -- one otherwise.  Measured on MI355X: two units per lane +2 to
-// +11% on copies; on an axpby walk of short misaligned rows -19%.
-template <int KIND, int MODE, bool HAS_T>
-constexpr int units_per_lane() {
-  return !HAS_T && (KIND == KIND_PACK || MODE == MODE_COPY) ? COSTA_COPY_UNITS : 1;
-}
-
-template <typename S, bool CPLX, int KIND, int MODE, bool CONJ, bool HAS_T>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8)))
-costa_mover(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks, int32_t task_off,
-            void* const* __restrict__ bufs, const ItemParam* __restrict__ items, int32_t allow_wide,
-            int32_t ranges) {
-  mover_body<S, CPLX, KIND, MODE, CONJ, HAS_T, units_per_lane<KIND, MODE, HAS_T>()>(pieces, tasks, task_off, bufs,
-                                                                                   items, allow_wide, ranges);
-}
-
-template <typename S, bool CPLX, int KIND, int MODE, bool CONJ, bool HAS_T>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8)))
-costa_mover_lds(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks, int32_t task_off,
-                void* const* __restrict__ bufs, const ItemParam* __restrict__ items, int32_t allow_wide,
-                int32_t ranges) {
-  mover_body<S, CPLX, KIND, MODE, CONJ, HAS_T, 1>(pieces, tasks, task_off, bufs, items, allow_wide, ranges);
+// One launch slice of LDS tiles, T lanes per workgroup; the other parameters
+// as above.
+template <typename S, bool CPLX, int KIND, int MODE, bool CONJ, int T>
+__global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(2, 8)))
+costa_tiles(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks, int32_t task_off,
+            void* const* __restrict__ bufs, const ItemParam* __restrict__ items, int32_t xcd_run) {
+  using TT = TypeTraits<S, CPLX>;
+  __shared__ Vec<S, TT::NS> lds[tile_lds_elems(TT::ES, T)];
+  const int32_t b = task_off + xcd_order((int32_t)blockIdx.x, (int32_t)gridDim.x, xcd_run);
+  const int32_t pi = tasks[b];
+  const int32_t c = b - pieces[pi].task0;
+  const ItemParam* ip = items + pieces[pi].item;
+  if constexpr (MODE != MODE_ANY) {
+    tile_task<S, CPLX, MODE, CONJ, T>(pieces, pi, c, bufs, ip, xcd_run, lds);
+  } else {
+#define COSTA_TASK(M, CJ) tile_task<S, CPLX, M, CJ, T>(pieces, pi, c, bufs, ip, xcd_run, lds)
+    COSTA_BY_MODE(COSTA_TASK);
+#undef COSTA_TASK
+  }
 }
 
 // Volume of the grid overlay: every overlay block (k, l) adds its element
@@ -765,7 +790,7 @@ struct Launch {
   void* const* bufs;
   const ItemParam* items;
   int32_t allow_wide;
-  int32_t ranges;
+  int32_t xcd_run;
 };
 
 // Separable volume, step 1: histogram of overlay interval lengths by (class
@@ -799,60 +824,73 @@ __global__ void __launch_bounds__(kThreads) costa_volume_outer(SeparableArgs a) 
 
 // One workgroup per task of the table the launch runs on, in slices that
 // keep the grid below 2^32 work-items.
-template <typename S, bool CPLX, int KIND, int MODE, bool CONJ, bool HAS_T>
-hipError_t go(const Launch& l) {
-  constexpr bool WIDE = units_per_lane<KIND, MODE, HAS_T>() > 1;
-  const int32_t* tasks = WIDE ? l.wide : l.tasks;
-  const int64_t ntasks = WIDE ? l.nwide : l.ntasks;
+template <typename F>
+hipError_t in_slices(int64_t ntasks, F&& launch) {
   if (ntasks > INT32_MAX) return hipErrorInvalidValue;
   constexpr int64_t kSlice = (int64_t)1 << 23;
   for (int64_t off = 0; off < ntasks; off += kSlice) {
-    const unsigned n = (unsigned)(ntasks - off < kSlice ? ntasks - off : kSlice);
-    if constexpr (big_lds<S, CPLX, HAS_T>())
-      hipLaunchKernelGGL((costa_mover_lds<S, CPLX, KIND, MODE, CONJ, HAS_T>), dim3(n), dim3(kThreads), 0, l.stream,
-                         l.pieces, tasks, (int32_t)off, l.bufs, l.items, l.allow_wide, l.ranges);
-    else
-      hipLaunchKernelGGL((costa_mover<S, CPLX, KIND, MODE, CONJ, HAS_T>), dim3(n), dim3(kThreads), 0, l.stream,
-                         l.pieces, tasks, (int32_t)off, l.bufs, l.items, l.allow_wide, l.ranges);
+    launch((unsigned)(ntasks - off < kSlice ? ntasks - off : kSlice), (int32_t)off);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-template <typename S, bool CPLX, int KIND, bool HAS_T>
-hipError_t go_mode(const Launch& l, int mode, int conj) {
+template <typename S, bool CPLX, int KIND, int MODE, bool CONJ>
+hipError_t go_walks(const Launch& l) {
+  constexpr bool WIDE = units_per_lane<KIND, MODE>() > 1;
+  const int32_t* tasks = WIDE ? l.wide : l.tasks;
+  return in_slices(WIDE ? l.nwide : l.ntasks, [&](unsigned n, int32_t off) {
+    hipLaunchKernelGGL((costa_mover<S, CPLX, KIND, MODE, CONJ>), dim3(n), dim3(kThreads), 0, l.stream, l.pieces, tasks,
+                       off, l.bufs, l.items, l.allow_wide, l.xcd_run);
+  });
+}
+
+template <typename S, bool CPLX, int KIND, int MODE, bool CONJ, int T>
+hipError_t go_tiles(const Launch& l) {
+  return in_slices(l.ntasks, [&](unsigned n, int32_t off) {
+    hipLaunchKernelGGL((costa_tiles<S, CPLX, KIND, MODE, CONJ, T>), dim3(n), dim3(T), 0, l.stream, l.pieces, l.tasks,
+                       off, l.bufs, l.items, l.xcd_run);
+  });
+}
+
+template <typename S, bool CPLX, int KIND, int MODE, bool CONJ>
+hipError_t go(const Launch& l, int tile_lanes) {
+  if (tile_lanes == 0) return go_walks<S, CPLX, KIND, MODE, CONJ>(l);
+  if (tile_lanes == kSmallTileLanes) return go_tiles<S, CPLX, KIND, MODE, CONJ, kSmallTileLanes>(l);
+  return go_tiles<S, CPLX, KIND, MODE, CONJ, kThreads>(l);
+}
+
+template <typename S, bool CPLX, int KIND>
+hipError_t go_mode(const Launch& l, const LaunchSpec& spec) {
   // one mode for the whole call: its own kernel (the per-pair kernel holds
   // the registers of every mode: float tiles 86 against 50, five waves per
   // SIMD against eight)
-  if (mode == MODE_COPY) return conj ? go<S, CPLX, KIND, MODE_COPY, CPLX, HAS_T>(l)
-                                     : go<S, CPLX, KIND, MODE_COPY, false, HAS_T>(l);
-  if (mode == MODE_SCALE) return conj ? go<S, CPLX, KIND, MODE_SCALE, CPLX, HAS_T>(l)
-                                      : go<S, CPLX, KIND, MODE_SCALE, false, HAS_T>(l);
-  if (mode == MODE_AXPBY) return conj ? go<S, CPLX, KIND, MODE_AXPBY, CPLX, HAS_T>(l)
-                                      : go<S, CPLX, KIND, MODE_AXPBY, false, HAS_T>(l);
-  return go<S, CPLX, KIND, MODE_ANY, false, HAS_T>(l);
+  const int conj = spec.conj, tl = spec.tile_lanes;
+  if (spec.mode == MODE_COPY)
+    return conj ? go<S, CPLX, KIND, MODE_COPY, CPLX>(l, tl) : go<S, CPLX, KIND, MODE_COPY, false>(l, tl);
+  if (spec.mode == MODE_SCALE)
+    return conj ? go<S, CPLX, KIND, MODE_SCALE, CPLX>(l, tl) : go<S, CPLX, KIND, MODE_SCALE, false>(l, tl);
+  if (spec.mode == MODE_AXPBY)
+    return conj ? go<S, CPLX, KIND, MODE_AXPBY, CPLX>(l, tl) : go<S, CPLX, KIND, MODE_AXPBY, false>(l, tl);
+  return go<S, CPLX, KIND, MODE_ANY, false>(l, tl);
 }
 
 template <typename S, bool CPLX>
 hipError_t launch_typed(MoverKind kind, const LaunchSpec& spec, const Launch& l) {
-  if (kind == KIND_PACK) return go<S, CPLX, KIND_PACK, MODE_COPY, false, false>(l);
-  if (kind == KIND_UNPACK) {
-    return spec.has_transpose ? go_mode<S, CPLX, KIND_UNPACK, true>(l, spec.mode, spec.conj)
-                              : go_mode<S, CPLX, KIND_UNPACK, false>(l, spec.mode, spec.conj);
-  }
-  return spec.has_transpose ? go_mode<S, CPLX, KIND_DIRECT, true>(l, spec.mode, spec.conj)
-                            : go_mode<S, CPLX, KIND_DIRECT, false>(l, spec.mode, spec.conj);
+  if (kind == KIND_PACK) return go_walks<S, CPLX, KIND_PACK, MODE_COPY, false>(l);
+  if (kind == KIND_UNPACK) return go_mode<S, CPLX, KIND_UNPACK>(l, spec);
+  return go_mode<S, CPLX, KIND_DIRECT>(l, spec);
 }
 
 }  // namespace
 
 hipError_t launch_mover(MoverKind kind, costa_dtype dtype, const LaunchSpec& spec, const Piece* pieces,
                         const int32_t* tasks, int64_t ntasks, const int32_t* wide, int64_t nwide, void* const* bufs,
-                        const ItemParam* items, int32_t allow_wide, int32_t xcd_ranges, hipStream_t stream) {
+                        const ItemParam* items, int32_t allow_wide, int32_t xcd_run, hipStream_t stream) {
   if (ntasks <= 0) return hipSuccess;
-  if (!spec.has_transpose && nwide <= 0) return hipErrorInvalidValue;  // a launch of row walks has both tables
-  Launch l{stream, pieces, tasks, ntasks, wide, nwide, bufs, items, allow_wide, xcd_ranges};
+  if (!spec.tile_lanes && nwide <= 0) return hipErrorInvalidValue;  // a launch of row walks has both tables
+  Launch l{stream, pieces, tasks, ntasks, wide, nwide, bufs, items, allow_wide, xcd_run};
   switch (dtype) {
     case COSTA_R64: return launch_typed<double, false>(kind, spec, l);
     case COSTA_C128: return launch_typed<double, true>(kind, spec, l);

@@ -391,8 +391,7 @@ void finish_piece(Piece& p, int elem_size) {
   p.aux = 0;
   if (p.flags & PIECE_TRANSPOSE) {
     int32_t tx, ty;
-    const bool aligned_cols = p.src_off * elem_size % 128 == 0 && (p.nx == 1 || p.src_ld * elem_size % 128 == 0);
-    choose_tile(elem_size, p.nx, p.ny, aligned_cols, tx, ty);
+    choose_tile(elem_size, kThreadsPerTask, p.nx, p.ny, tx, ty);
     p.aux = tile_pack(tx, ty);
     return;
   }
@@ -439,6 +438,15 @@ void finish_piece(Piece& p, int elem_size) {
 #ifndef COSTA_XCD_DENSE
 #define COSTA_XCD_DENSE 0
 #endif
+
+// Tiles an XCD takes at a time in launches of tiles that read A and of which
+// two thirds start or end a row inside a 128-byte line of A: the line is then
+// read once by the XCD that moves both neighbours.  Measured on MI355X (one
+// tile at a time against 16): 22 x 22-element tiles, float 322 -> 277 us,
+// double 271 -> 216, complex128 171 -> 159; pztranc 682 -> 658 us; runs of 4
+// and 64 within 4%.  Launches that copy lose (pdtran 850 -> 905), and so do
+// those where half of the rows end on a line (12 x 12 doubles 249 -> 267).
+constexpr int32_t kTileRun = 16;
 
 // Whether every run of the rectangle (its rows in the source and in the
 // destination) starts and ends on a 128-byte line.
@@ -530,12 +538,34 @@ void fill_tasks(std::vector<int32_t>& table, const std::vector<std::pair<int64_t
   });
 }
 
+// The lanes per workgroup of a launch's LDS tiles: kSmallTileLanes when the
+// tiles chosen so far average at most small_tile_mean elements (its rectangles
+// are then cut anew for the smaller tile), else kThreadsPerTask.
+int32_t pick_tile_lanes(std::vector<Piece>& ps, int es, bool small_tiles) {
+  int64_t elems = 0, tiles = 0;
+  for (const Piece& p : ps) {
+    if (!(p.flags & PIECE_TRANSPOSE)) continue;
+    const int32_t tx = tile_x_of(p.aux), ty = tile_y_of(p.aux);
+    elems += (int64_t)p.nx * p.ny;
+    tiles += (int64_t)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
+  }
+  if (!small_tiles || elems > tiles * small_tile_mean(es)) return kThreadsPerTask;
+  for (Piece& p : ps) {
+    if (!(p.flags & PIECE_TRANSPOSE)) continue;
+    int32_t tx, ty;
+    choose_tile(es, kSmallTileLanes, p.nx, p.ny, tx, ty);
+    p.aux = tile_pack(tx, ty);
+  }
+  return kSmallTileLanes;
+}
+
 // Appends one launch: its rectangles and the workgroups that move them, in
 // rectangle order.  A transposed rectangle gets one workgroup per LDS tile
 // (tiles along x first); a row walk one per kThreadsPerTask units; runs of
 // small row walks of the same pair and vector width share one workgroup; a
 // stack the workgroups of its bands (stack_tasks).
-LaunchRange add_launch(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nitems, bool is_pack) {
+LaunchRange add_launch(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nitems, bool is_pack, bool small_tiles) {
+  const int32_t tile_lanes = pick_tile_lanes(ps, es, small_tiles);
   LaunchRange lr;
   lr.item_elems.assign(nitems, 0);
   lr.piece_begin = (int64_t)hp.pieces.size();
@@ -583,7 +613,7 @@ LaunchRange add_launch(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nit
       continue;
     }
     if (p.flags & PIECE_TRANSPOSE) {
-      lr.has_transpose = true;
+      lr.tile_lanes = tile_lanes;
       g_task = -1;
       const int32_t tx = tile_x_of(p.aux), ty = tile_y_of(p.aux);
       const int64_t n = (int64_t)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
@@ -634,7 +664,7 @@ LaunchRange add_launch(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nit
   // the wide task table of a launch of row walks: kWideTaskUnits units per
   // task, a run of small rectangles still one task
   lr.wide_begin = (int64_t)hp.wide_tasks.size();
-  if (!lr.has_transpose) {
+  if (!lr.tile_lanes) {
     int64_t b2 = 0;
     seg.clear();
     for (size_t k = 0; k < ps.size(); ++k) {
@@ -660,16 +690,21 @@ LaunchRange add_launch(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nit
     lr.nwide = b2;
     if (need_wide) fill_tasks(hp.wide_tasks, seg, b2);
   }
-  int64_t aligned = 0, transposed = 0, far = 0, near = 0, dense = 0;
+  int64_t aligned = 0, transposed = 0, far = 0, near = 0, dense = 0, shared = 0;
   for (const Piece& p : ps) {
     const int64_t ne = (int64_t)p.nx * p.ny;
+    if (p.dst_off * es % 128 != 0 || (p.dst_off + p.nx) * es % 128 != 0) shared += ne;
     if (!(p.flags & PIECE_TRANSPOSE) && (p.ny == 1 || (p.src_ld == p.nx && p.dst_ld == p.nx))) dense += ne;
     if (line_aligned(p, es) || (COSTA_XCD_STACKS && (p.flags & PIECE_STACK))) aligned += ne;
     if (p.flags & PIECE_TRANSPOSE) transposed += ne;
     else if (p.ny > 1) (std::max(p.src_ld, p.dst_ld) * es >= COSTA_PACK_FAR_ROWS ? far : near) += ne;
   }
   const bool one_kind = (transposed == 0 || transposed == lr.elems) && (far == 0 || near == 0);
-  lr.xcd_ranges = COSTA_XCD_RANGES && one_kind && (COSTA_XCD_DENSE || dense < lr.elems) && lr.elems > 0 && 10 * aligned >= COSTA_XCD_ALIGNED_TENTHS * lr.elems ? 1 : 0;
+  if (COSTA_XCD_RANGES && one_kind && (COSTA_XCD_DENSE || dense < lr.elems) && lr.elems > 0 &&
+      10 * aligned >= COSTA_XCD_ALIGNED_TENTHS * lr.elems)
+    lr.xcd_run = -1;
+  else if (lr.tile_lanes && plan_reads_a && 3 * shared >= 2 * lr.elems)
+    lr.xcd_run = kTileRun;
   hp.pieces.insert(hp.pieces.end(), ps.begin(), ps.end());
   return lr;
 }
@@ -677,30 +712,25 @@ LaunchRange add_launch(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nit
 #ifndef COSTA_PACK_BY_SOURCE
 #define COSTA_PACK_BY_SOURCE 1
 #endif
-// Split an unpack or direct launch that holds both row walks and LDS tiles
-// into one launch of each kind (tiles first), so that each can take the
-// per-XCD workgroup ranges (measured on MI355X: tall-skinny batch of 4
-// identity + 4 transposed pairs: unpack +8%, whole step +4%).
-#ifndef COSTA_SPLIT_KINDS
-#define COSTA_SPLIT_KINDS 1
-#endif
-
-// The launches of one kernel kind over `ps` (sorted): one, or a tile launch
-// and a row-walk launch.
-std::vector<LaunchRange> add_launches(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nitems) {
+// The launches of one kernel kind over `ps` (sorted): one, or a launch of the
+// LDS tiles and one of the row walks, so that each can take the per-XCD
+// workgroup ranges (measured on MI355X: tall-skinny batch of 4 identity + 4
+// transposed pairs: unpack +8%, whole step +4%) and the kernel of its kind.
+std::vector<LaunchRange> add_launches(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nitems,
+                                      bool small_tiles) {
   std::vector<LaunchRange> out;
   if (ps.empty()) return out;
   std::vector<Piece> tiles, walks;
   size_t ntiles = 0;
   for (const Piece& p : ps) ntiles += (p.flags & PIECE_TRANSPOSE) ? 1 : 0;
-  if (COSTA_SPLIT_KINDS && ntiles > 0 && ntiles < ps.size()) {
+  if (ntiles > 0 && ntiles < ps.size()) {
     for (const Piece& p : ps) ((p.flags & PIECE_TRANSPOSE) ? tiles : walks).push_back(p);
   }
   if (tiles.empty() || walks.empty()) {
-    out.push_back(add_launch(hp, ps, es, nitems, false));
+    out.push_back(add_launch(hp, ps, es, nitems, false, small_tiles));
   } else {
-    out.push_back(add_launch(hp, tiles, es, nitems, false));
-    out.push_back(add_launch(hp, walks, es, nitems, false));
+    out.push_back(add_launch(hp, tiles, es, nitems, false, small_tiles));
+    out.push_back(add_launch(hp, walks, es, nitems, false, small_tiles));
   }
   return out;
 }
@@ -910,12 +940,12 @@ void build_plan(const std::vector<ItemDesc>& items, const std::vector<int32_t>& 
     sort_by_key(unpack, dst_key);
     Wave w;
     w.msg_bytes = off;
-    w.pack = add_launch(hp, pack, es, n, true);
-    w.unpack = add_launches(hp, unpack, es, n);
+    w.pack = add_launch(hp, pack, es, n, true, false);
+    w.unpack = add_launches(hp, unpack, es, n, false);
     hp.workspace_bytes = std::max(hp.workspace_bytes, off);
     hp.waves.push_back(w);
   }
-  hp.direct = add_launches(hp, direct, es, n);  // empty when merged above
+  hp.direct = add_launches(hp, direct, es, n, !cfg.messages);  // empty when merged above
   hp.plan_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
 

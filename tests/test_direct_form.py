@@ -13,10 +13,29 @@ import torch
 import oracle
 import synth
 from replay import _combine, _index, many_rank_cases, random_stack_case, short_walk_cases, stack_cases
-from test_plan_replay import DIRECT, _descs, _written_mask, check_tasks, stack_walk_cover
+from test_plan_replay import CAP, DIRECT, MAXX, _descs, _written_mask, check_tasks, stack_walk_cover
 
 C = pytest.importorskip("paper_2106_06601_amd")
 BC, GEN, SL = synth.BlockCyclic, synth.General, synth.ScaLapack
+
+
+# elements and width of the tiles that one wave moves (launches of small tiles)
+SMALL, SMALL_X = {4: 1024, 8: 768, 16: 512}, 64
+
+
+def check_tiles(ps, es):
+    """A launch of tiles: workgroups numbered in rectangle order, one per
+    tile, and every tile within the limits of its launch's workgroups (256
+    lanes, or one wave)."""
+    shapes = [(int(p["tile_x"]), int(p["tile_y"])) for p in ps]
+    small = all(x <= SMALL_X and x * y <= SMALL[es] for x, y in shapes)
+    nxt = 0
+    for p, (x, y) in zip(ps, shapes):
+        nx, ny = int(p["nx"]), int(p["ny"])
+        assert int(p["flags"]) & 1 and 1 <= x <= nx and 1 <= y <= ny
+        assert x * (y | 1) <= (SMALL[es] + SMALL_X if small else CAP[es]) and x <= MAXX[es]
+        assert int(p["group"]) == nxt and int(p["ntasks"]) == -(-nx // x) * -(-ny // y)
+        nxt += int(p["ntasks"])
 
 
 def _random_workload(seed):
@@ -63,9 +82,12 @@ def test_direct_rectangles_reproduce_the_oracle(k):
     x = C.costa_plan_export_direct(w.dtype, descs, sigma)
     assert (x["kind"] == DIRECT).all()
     es, npt, n, P = synth.ITEMSIZE[w.dtype], oracle.NUMPY[w.dtype], len(w.items), w.items[0].A.nranks
-    check_tasks(x, es)
     for launch in np.unique(x["launch"]):
         ps = [p for p in x if p["launch"] == launch]
+        if int(ps[0]["flags"]) & 1:
+            check_tiles(ps, es)
+            continue
+        check_tasks(ps, es)
         assert all((cv == 1).all() for cv in stack_walk_cover(ps, es).values())
     sg = list(range(P)) if sigma is None else sigma
     inv = [sg.index(r) for r in range(P)]
@@ -98,6 +120,65 @@ def test_direct_rectangles_reproduce_the_oracle(k):
         for r in range(P):
             assert np.array_equal(hits[i * P + r], want[r]), "an element of A is not written exactly once"
             assert np.array_equal(bufs[i * P + r].view(u), ha[r].view(u))
+
+
+@pytest.mark.parametrize("lanes", [64, 256])
+def test_lanes_step_through_every_tile_element(lanes):
+    """A lane's steps (one division, then the same additions, and one more
+    past a row's end) visit every element of a tile once, at the memory offset
+    and LDS slot of its row and column."""
+    for rows, length in [(1, 1), (2, 3), (7, 64), (64, 7), (23, 37), (3, 255), (2, 257), (5, 300), (1, 1024), (128, 16)]:
+        ld, ls, lc = 1000003, length | 1, 1
+        q, rem = divmod(lanes, length)
+        seen = np.zeros((rows, length), int)
+        for tid in range(lanes):
+            row, col = divmod(tid, length)
+            off, slot = row * ld + col, row * ls + col * lc
+            for k in range(-(-rows * length // lanes)):
+                if k * lanes + tid < rows * length:
+                    r, c = off // ld, off % ld
+                    assert slot == r * ls + c * lc
+                    seen[r, c] += 1
+                col += rem
+                wrap = col >= length
+                col -= length if wrap else 0
+                off += q * ld + rem + (ld - length if wrap else 0)
+                slot += q * ls + rem * lc + (ls - length * lc if wrap else 0)
+        assert (seen == 1).all()
+
+
+def test_division_by_reciprocal_needs_one_step():
+    """The kernels' u / n: float(u) * rcp(n), truncated, is at most one off
+    for u < 2^22 + 1024 (row walks, tiles) and, for n >= 2, for u < 2^23
+    (stacks), with the reciprocal anywhere within one ulp."""
+    rng = np.random.default_rng(5)
+    for top, first in (((1 << 22) + 1024, 1), (1 << 23, 2)):
+        n = np.concatenate([np.arange(first, 3000), rng.integers(first, top, 3000)]).astype(np.int64)
+        base = np.float32(1) / n.astype(np.float32)
+        for k in (1, 2, 3, 1 << 10, 1 << 20, 1 << 30):
+            m = np.minimum(np.minimum(k, (top - 1) // n) * n, top - 1)  # multiples of n, and the last ones
+            for u in (m, np.maximum(m - 1, 0), np.minimum(m + 1, top - 1)):
+                for rcp in (base, np.nextafter(base, np.float32(0)), np.nextafter(base, np.float32(2))):
+                    y = (u.astype(np.float32) * rcp).astype(np.int64)
+                    assert (np.abs(y - u // n) <= 1).all()
+
+
+@pytest.mark.parametrize("run", [-1, 0, 16])
+def test_workgroup_order_is_a_permutation(run):
+    for n in (1, 7, 8, 127, 128, 129, 1000, 4096, 4100):
+        out = []
+        for b in range(n):
+            xcd, idx = b % 8, b // 8
+            if run == 0:
+                t = b
+            elif run > 0:
+                turn = idx // run
+                t = b if (turn + 1) * 8 * run > n else (turn * 8 + xcd) * run + idx - turn * run
+            else:
+                q, r = n // 8, n % 8
+                t = (xcd * (q + 1) if xcd < r else r * (q + 1) + (xcd - r) * q) + idx
+            out.append(t)
+        assert sorted(out) == list(range(n))
 
 
 # ---------------------------------------------------------------------------
