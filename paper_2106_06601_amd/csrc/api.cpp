@@ -41,14 +41,15 @@ bool is_complex(costa_dtype d) { return d == COSTA_C128 || d == COSTA_C64; }
 struct DevicePlan {
   HostPlan host;
   int device = -1;
+  // the plan's rectangles and task tables, in one allocation
+  void* d_tables = nullptr;
   Piece* d_pieces = nullptr;
   int32_t* d_tasks = nullptr;
   int32_t* d_wide = nullptr;
-  // per-call table: buffer pointers then pair parameters
+  // the call table of calls whose table is too large for kernel arguments
+  // (made by the first of them)
   void* d_table = nullptr;
   void* h_staging = nullptr;  // pinned
-  size_t table_bytes = 0;
-  size_t nbufs = 0;
   std::vector<unsigned char> last_table;
   hipEvent_t table_event = nullptr;  // the last table upload (h_staging reusable after it)
   bool table_pending = false;
@@ -56,9 +57,7 @@ struct DevicePlan {
   hipStream_t last_stream = nullptr;
   bool used = false;
   ~DevicePlan() {
-    if (d_pieces) (void)hipFree(d_pieces);
-    if (d_tasks) (void)hipFree(d_tasks);
-    if (d_wide) (void)hipFree(d_wide);
+    if (d_tables) (void)hipFree(d_tables);
     if (d_table) (void)hipFree(d_table);
     if (h_staging) (void)hipHostFree(h_staging);
     if (table_event) (void)hipEventDestroy(table_event);
@@ -268,7 +267,7 @@ struct DeviceTables {
 // Launches one mover range, bracketed by timing events when enabled (and
 // `timed`).
 costa_status run_range(State& S, MoverKind kind, costa_dtype dt, const DeviceTables& dt_, const LaunchRange& lr,
-                       int32_t mode, int32_t conj, void* const* d_bufs, const ItemParam* d_items, int32_t allow_wide,
+                       int32_t mode, int32_t conj, const CallTable& table, int32_t allow_wide,
                        int64_t bytes, hipStream_t stream, bool timed = true) {
   if (lr.ntasks == 0) return COSTA_SUCCESS;
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -290,7 +289,7 @@ costa_status run_range(State& S, MoverKind kind, costa_dtype dt, const DeviceTab
   }
   LaunchSpec spec{mode, conj, lr.tile_lanes};
   HIP_OR_FAIL(launch_mover(kind, dt, spec, dt_.pieces, dt_.tasks + lr.task_begin, lr.ntasks,
-                           lr.nwide ? dt_.wide + lr.wide_begin : nullptr, lr.nwide, d_bufs, d_items, allow_wide,
+                           lr.nwide ? dt_.wide + lr.wide_begin : nullptr, lr.nwide, table, allow_wide,
                            lr.xcd_run, stream));
   if (e1) {
     HIP_OR_FAIL(hipEventRecord(e1, stream));
@@ -368,33 +367,41 @@ costa_status get_plan(State& S, int device, Form form, costa_dtype dt, const std
   }
   const HostPlan& hp = dp->host;
   if (!hp.pieces.empty()) {
-    HIP_OR_FAIL(hipMalloc(&dp->d_pieces, hp.pieces.size() * sizeof(Piece)));
-    HIP_OR_FAIL(hipMemcpy(dp->d_pieces, hp.pieces.data(), hp.pieces.size() * sizeof(Piece), hipMemcpyHostToDevice));
-    HIP_OR_FAIL(hipMalloc(&dp->d_tasks, hp.tasks.size() * sizeof(int32_t)));
-    HIP_OR_FAIL(hipMemcpy(dp->d_tasks, hp.tasks.data(), hp.tasks.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    if (!hp.wide_tasks.empty()) {
-      HIP_OR_FAIL(hipMalloc(&dp->d_wide, hp.wide_tasks.size() * sizeof(int32_t)));
-      HIP_OR_FAIL(hipMemcpy(dp->d_wide, hp.wide_tasks.data(), hp.wide_tasks.size() * sizeof(int32_t),
-                            hipMemcpyHostToDevice));
+    // one allocation, and for small plans one copy (each costs a first call
+    // some 10 us)
+    struct Part {
+      const void* src;
+      size_t bytes, at;
+    } part[3] = {{hp.pieces.data(), hp.pieces.size() * sizeof(Piece), 0},
+                 {hp.tasks.data(), hp.tasks.size() * sizeof(int32_t), 0},
+                 {hp.wide_tasks.data(), hp.wide_tasks.size() * sizeof(int32_t), 0}};
+    size_t total = 0;
+    for (Part& q : part) {
+      q.at = total;
+      total += (q.bytes + 255) / 256 * 256;
     }
+    HIP_OR_FAIL(hipMalloc(&dp->d_tables, total));
+    unsigned char* base = static_cast<unsigned char*>(dp->d_tables);
+    if (total <= (1u << 20)) {
+      std::vector<unsigned char> all(total, 0);
+      for (const Part& q : part)
+        if (q.bytes) std::memcpy(all.data() + q.at, q.src, q.bytes);
+      HIP_OR_FAIL(hipMemcpy(base, all.data(), total, hipMemcpyHostToDevice));
+    } else {
+      for (const Part& q : part)
+        if (q.bytes) HIP_OR_FAIL(hipMemcpy(base + q.at, q.src, q.bytes, hipMemcpyHostToDevice));
+    }
+    dp->d_pieces = reinterpret_cast<Piece*>(base);
+    dp->d_tasks = reinterpret_cast<int32_t*>(base + part[1].at);
+    dp->d_wide = reinterpret_cast<int32_t*>(base + part[2].at);
   }
-  const int32_t P = items.empty() ? 0 : items[0].A->nranks;
-  dp->nbufs = (size_t)2 * items.size() * P + 1;
-  size_t ptr_bytes = (dp->nbufs * sizeof(void*) + 63) / 64 * 64;
-  dp->table_bytes = ptr_bytes + items.size() * sizeof(ItemParam);
-  HIP_OR_FAIL(hipMalloc(&dp->d_table, dp->table_bytes));
-  HIP_OR_FAIL(hipHostMalloc(&dp->h_staging, dp->table_bytes, hipHostMallocDefault));
-  HIP_OR_FAIL(hipEventCreateWithFlags(&dp->table_event, hipEventDisableTiming));
-  HIP_OR_FAIL(hipEventCreateWithFlags(&dp->last_use, hipEventDisableTiming));
   out = dp.get();
   S.plans.emplace(key, std::move(dp));
   return COSTA_SUCCESS;
 }
 
-// The table a call's kernels read: the buffer pointers (A of pair k, rank r
-// at k*P + r; B at n*P + k*P + s; the message workspace at 2*n*P), padded to
-// 64 bytes, then one ItemParam per pair.  Returns the pointers' byte size;
-// reads_a[k]: pair k reads A (beta != 0); aligned: every buffer 16-byte
+// The table a call's kernels read (see CallTable).  Returns the pointers' byte
+// size; reads_a[k]: pair k reads A (beta != 0); aligned: every buffer 16-byte
 // aligned.
 size_t call_table(costa_dtype dt, int32_t n, const costa_transform_desc* desc, int32_t P, void* messages,
                   std::vector<unsigned char>& table, std::vector<char>& reads_a, bool& aligned) {
@@ -439,6 +446,7 @@ bool a_overlaps_b(int es, int32_t n, const costa_transform_desc* desc, const std
   };
   std::vector<Range> v;
   v.reserve((size_t)2 * n * P);
+  uintptr_t lo[2] = {UINTPTR_MAX, UINTPTR_MAX}, hi[2] = {0, 0};  // all of B, all of A
   for (int32_t k = 0; k < n; ++k)
     for (int32_t t = 0; t < P; ++t) {
       const int32_t r = sig.empty() ? t : sig[t];
@@ -447,6 +455,11 @@ bool a_overlaps_b(int es, int32_t n, const costa_transform_desc* desc, const std
       if (na) v.push_back(Range{a, a + na, true});
       if (nb) v.push_back(Range{b, b + nb, false});
     }
+  for (const Range& r : v) {
+    lo[r.is_a] = std::min(lo[r.is_a], r.lo);
+    hi[r.is_a] = std::max(hi[r.is_a], r.hi);
+  }
+  if (hi[0] <= lo[1] || hi[1] <= lo[0]) return false;
   std::sort(v.begin(), v.end(), [](const Range& x, const Range& y) { return x.lo < y.lo; });
   uintptr_t end_a = 0, end_b = 0;  // the furthest end so far of either kind
   for (const Range& r : v) {
@@ -461,7 +474,7 @@ bool a_overlaps_b(int es, int32_t n, const costa_transform_desc* desc, const std
 // pack and unpack-transform of each wave.
 costa_status launch_plan(State& S, costa_dtype dt, const HostPlan& hp, const DeviceTables& tabs,
                          const ItemParam* ipar, int32_t n, const std::vector<char>& reads_a, bool aligned,
-                         void* const* d_bufs, const ItemParam* d_items, hipStream_t stream, bool timed) {
+                         const CallTable& table, hipStream_t stream, bool timed) {
   const int es = elem_size(dt);
   const int32_t wide = aligned ? 1 : 0;
   // one arithmetic mode for the whole call when every pair agrees
@@ -470,21 +483,43 @@ costa_status launch_plan(State& S, costa_dtype dt, const HostPlan& hp, const Dev
     if (ipar[k].mode != mode || ipar[k].conj != conj) mode = -1;
   costa_status st;
   for (const LaunchRange& lr : hp.direct) {
-    st = run_range(S, KIND_DIRECT, dt, tabs, lr, mode, conj, d_bufs, d_items, wide, range_bytes(lr, es, reads_a),
+    st = run_range(S, KIND_DIRECT, dt, tabs, lr, mode, conj, table, wide, range_bytes(lr, es, reads_a),
                    stream, timed);
     if (st != COSTA_SUCCESS) return st;
   }
   std::vector<char> no_read(n, 0);
   for (const Wave& w : hp.waves) {
-    st = run_range(S, KIND_PACK, dt, tabs, w.pack, MODE_COPY, 0, d_bufs, d_items, wide,
+    st = run_range(S, KIND_PACK, dt, tabs, w.pack, MODE_COPY, 0, table, wide,
                    range_bytes(w.pack, es, no_read), stream, timed);
     if (st != COSTA_SUCCESS) return st;
     for (const LaunchRange& lr : w.unpack) {
-      st = run_range(S, KIND_UNPACK, dt, tabs, lr, mode, conj, d_bufs, d_items, wide, range_bytes(lr, es, reads_a),
+      st = run_range(S, KIND_UNPACK, dt, tabs, lr, mode, conj, table, wide, range_bytes(lr, es, reads_a),
                      stream, timed);
       if (st != COSTA_SUCCESS) return st;
     }
   }
+  return COSTA_SUCCESS;
+}
+
+// Puts a call's table into the plan's device copy, unless it holds it already.
+costa_status upload_table(DevicePlan& dp, const std::vector<unsigned char>& table, hipStream_t stream) {
+  if (!dp.last_use) {
+    if (!dp.d_table) HIP_OR_FAIL(hipMalloc(&dp.d_table, table.size()));
+    if (!dp.h_staging) HIP_OR_FAIL(hipHostMalloc(&dp.h_staging, table.size(), hipHostMallocDefault));
+    if (!dp.table_event) HIP_OR_FAIL(hipEventCreateWithFlags(&dp.table_event, hipEventDisableTiming));
+    HIP_OR_FAIL(hipEventCreateWithFlags(&dp.last_use, hipEventDisableTiming));
+  }
+  if (table == dp.last_table) return COSTA_SUCCESS;
+  // the kernels of the plan's last call read the table until they end: on
+  // another stream, the new table is written only after them
+  if (dp.used && dp.last_stream != stream) HIP_OR_FAIL(hipStreamWaitEvent(stream, dp.last_use, 0));
+  if (dp.table_pending) HIP_OR_FAIL(hipEventSynchronize(dp.table_event));
+  std::memcpy(dp.h_staging, table.data(), table.size());
+  dp.last_table.clear();
+  HIP_OR_FAIL(hipMemcpyAsync(dp.d_table, dp.h_staging, table.size(), hipMemcpyHostToDevice, stream));
+  HIP_OR_FAIL(hipEventRecord(dp.table_event, stream));
+  dp.table_pending = true;
+  dp.last_table = table;
   return COSTA_SUCCESS;
 }
 
@@ -528,32 +563,30 @@ costa_status transform_impl(costa_dtype dt, int32_t n, const costa_transform_des
     reinterpret_cast<void**>(table.data())[(size_t)2 * n * P] = ws->ptr;
     if (ws->used && ws->last_stream != stream) HIP_OR_FAIL(hipStreamWaitEvent(stream, ws->last_use, 0));
   }
-  if (table != dp->last_table) {
-    // the kernels of the plan's last call read the table until they end: on
-    // another stream, the new table is written only after them
-    if (dp->used && dp->last_stream != stream) HIP_OR_FAIL(hipStreamWaitEvent(stream, dp->last_use, 0));
-    if (dp->table_pending) HIP_OR_FAIL(hipEventSynchronize(dp->table_event));
-    std::memcpy(dp->h_staging, table.data(), table.size());
-    HIP_OR_FAIL(hipMemcpyAsync(dp->d_table, dp->h_staging, table.size(), hipMemcpyHostToDevice, stream));
-    HIP_OR_FAIL(hipEventRecord(dp->table_event, stream));
-    dp->table_pending = true;
-    dp->last_table.swap(table);
+  ArgTable args;
+  CallTable ct{nullptr, nullptr, (int32_t)ptr_bytes};
+  if (table.size() <= sizeof args) {
+    std::memcpy(args.bytes, table.data(), table.size());
+    ct.args = &args;
+  } else {
+    st = upload_table(*dp, table, stream);
+    if (st != COSTA_SUCCESS) return st;
+    ct.device = dp->d_table;
   }
-
-  void* const* d_bufs = reinterpret_cast<void* const*>(dp->d_table);
-  const ItemParam* d_items = reinterpret_cast<const ItemParam*>((unsigned char*)dp->d_table + ptr_bytes);
-  const ItemParam* ipar = reinterpret_cast<const ItemParam*>(dp->last_table.data() + ptr_bytes);
-  st = launch_plan(S, dt, hp, DeviceTables{dp->d_pieces, dp->d_tasks, dp->d_wide}, ipar, n, reads_a, aligned,
-                   d_bufs, d_items, stream, true);
+  const ItemParam* ipar = reinterpret_cast<const ItemParam*>(table.data() + ptr_bytes);
+  st = launch_plan(S, dt, hp, DeviceTables{dp->d_pieces, dp->d_tasks, dp->d_wide}, ipar, n, reads_a, aligned, ct,
+                   stream, true);
   if (st != COSTA_SUCCESS) return st;
   if (ws) {
     HIP_OR_FAIL(hipEventRecord(ws->last_use, stream));
     ws->last_stream = stream;
     ws->used = true;
   }
-  HIP_OR_FAIL(hipEventRecord(dp->last_use, stream));
-  dp->last_stream = stream;
-  dp->used = true;
+  if (ct.device) {
+    HIP_OR_FAIL(hipEventRecord(dp->last_use, stream));
+    dp->last_stream = stream;
+    dp->used = true;
+  }
   return COSTA_SUCCESS;
 }
 
@@ -1064,18 +1097,25 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
     std::vector<char> reads_a;
     bool aligned = true;
     const size_t ptr_bytes = call_table(dtype, n, desc, P, base + kNoallocTableBytes, table, reads_a, aligned);
-    if (table != dev->table) {
-      HIP_OR_FAIL(hipMemcpyAsync(base + np->off_table, table.data(), table.size(), hipMemcpyHostToDevice, stream));
-      dev->table.swap(table);
+    ArgTable args;
+    CallTable ct{nullptr, nullptr, (int32_t)ptr_bytes};
+    if (table.size() <= sizeof args) {
+      std::memcpy(args.bytes, table.data(), table.size());
+      ct.args = &args;
+    } else {
+      if (table != dev->table) {
+        dev->table.clear();
+        HIP_OR_FAIL(hipMemcpyAsync(base + np->off_table, table.data(), table.size(), hipMemcpyHostToDevice, stream));
+        dev->table = table;
+      }
+      ct.device = base + np->off_table;
     }
-    const ItemParam* ipar = reinterpret_cast<const ItemParam*>(dev->table.data() + ptr_bytes);
-    void* const* d_bufs = reinterpret_cast<void* const*>(base + np->off_table);
-    const ItemParam* d_items = reinterpret_cast<const ItemParam*>(base + np->off_table + ptr_bytes);
+    const ItemParam* ipar = reinterpret_cast<const ItemParam*>(table.data() + ptr_bytes);
     const DeviceTables tabs{reinterpret_cast<const Piece*>(base),
                             reinterpret_cast<const int32_t*>(base + np->off_tasks),
                             reinterpret_cast<const int32_t*>(base + np->off_wide)};
     // no timing events on this path (creating one may allocate)
-    return launch_plan(S, dtype, hp, tabs, ipar, n, reads_a, aligned, d_bufs, d_items, stream, false);
+    return launch_plan(S, dtype, hp, tabs, ipar, n, reads_a, aligned, ct, stream, false);
   });
 }
 

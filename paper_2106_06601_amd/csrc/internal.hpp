@@ -279,6 +279,21 @@ struct alignas(16) ItemParam {
 };
 static_assert(sizeof(ItemParam) == 48, "ItemParam must be 48 bytes");
 
+// The table of a call: its buffer pointers (A of pair k, rank r at k*P + r; B
+// at n*P + k*P + s; the message workspace at 2*n*P), padded to 64 bytes, then
+// one ItemParam per pair.  Tables of up to kArgTableBytes travel as kernel
+// arguments (one pair of up to 120 ranks, eight pairs of 12); larger ones are
+// in device memory.
+constexpr size_t kArgTableBytes = 2048;
+struct alignas(16) ArgTable {
+  unsigned char bytes[kArgTableBytes];
+};
+struct CallTable {
+  const ArgTable* args;   // the table, or null
+  const void* device;     // the table in device memory where args is null
+  int32_t items_off;      // byte offset of the ItemParams
+};
+
 // One kernel launch of a plan: a range of rectangles and the workgroups
 // (tasks) that move them.  tasks[task_begin + b] = index into Plan::pieces of
 // the rectangle task b starts with; that rectangle's task0 is the first task
@@ -320,8 +335,8 @@ struct LaunchSpec {
 // tasks in turn; -1 hands each XCD one contiguous range of the tasks of each
 // launch slice.
 hipError_t launch_mover(MoverKind kind, costa_dtype dtype, const LaunchSpec& spec, const Piece* pieces,
-                        const int32_t* tasks, int64_t ntasks, const int32_t* wide, int64_t nwide, void* const* bufs,
-                        const ItemParam* items, int32_t allow_wide, int32_t xcd_run, hipStream_t stream);
+                        const int32_t* tasks, int64_t ntasks, const int32_t* wide, int64_t nwide,
+                        const CallTable& table, int32_t allow_wide, int32_t xcd_run, hipStream_t stream);
 
 struct VolumeArgs {
   const Interval* rows;

@@ -96,6 +96,17 @@ struct Raw<16> {
 // (not flat) loads and stores, which do not share a wait counter with LDS.
 #define COSTA_GLOBAL __attribute__((address_space(1)))
 
+// The call's table (CallTable), read with scalar loads from the kernel's own
+// arguments (ArgTable is the first parameter of every mover, so it starts the
+// argument segment) or from device memory; `device` is the same for every
+// lane.
+#define COSTA_CONST __attribute__((address_space(4)))
+using Bufs = void* const COSTA_CONST*;
+using Items = const ItemParam COSTA_CONST*;
+__device__ __forceinline__ const char COSTA_CONST* call_table(const void* device) {
+  return device ? (const char COSTA_CONST*)device : (const char COSTA_CONST*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 template <bool NT = COSTA_NT_LOADS, typename U>
 __device__ __forceinline__ U load(const U* p) {
   using R = typename Raw<sizeof(U)>::T;
@@ -223,7 +234,7 @@ struct TileWalk {
 // before its stores.
 template <typename S, bool CPLX, int MODE, bool CONJ, int UL>
 __device__ __forceinline__ void move_walk(const Piece* __restrict__ pieces, int32_t pi, int32_t u0,
-                                          void* const* __restrict__ bufs, int32_t allow_wide, S ar, S ai, S br,
+                                          Bufs bufs, int32_t allow_wide, S ar, S ai, S br,
                                           S bi) {
   using TT = TypeTraits<S, CPLX>;
   using E = Vec<S, TT::NS>;
@@ -336,7 +347,7 @@ __device__ __forceinline__ void move_walk(const Piece* __restrict__ pieces, int3
 // (c+1)*UL*kThreads) of its flattened (y, x) index.
 template <typename S, bool CPLX, int MODE, bool CONJ, int UL>
 __device__ __forceinline__ void move_walk_lanes(const Piece* __restrict__ pieces, int32_t pi, int32_t c,
-                                          void* const* __restrict__ bufs, int32_t allow_wide, S ar, S ai, S br,
+                                          Bufs bufs, int32_t allow_wide, S ar, S ai, S br,
                                           S bi) {
   using TT = TypeTraits<S, CPLX>;
   using E = Vec<S, TT::NS>;
@@ -432,7 +443,7 @@ constexpr int kStackRowsInFlight = COSTA_STACK_ROWS_IN_FLIGHT;
 
 template <typename S, bool CPLX, int MODE, bool CONJ>
 __device__ __forceinline__ void move_stack(const Piece* __restrict__ pieces, int32_t pi, int32_t c,
-                                           void* const* __restrict__ bufs, int32_t allow_wide, S ar, S ai, S br,
+                                           Bufs bufs, int32_t allow_wide, S ar, S ai, S br,
                                            S bi) {
   using TT = TypeTraits<S, CPLX>;
   using E = Vec<S, TT::NS>;
@@ -554,7 +565,7 @@ __device__ __forceinline__ void move_stack(const Piece* __restrict__ pieces, int
 // for a full memory round trip.
 template <typename S, bool CPLX, int MODE, bool CONJ, int T>
 __device__ __forceinline__ void move_tile(const Piece* __restrict__ pieces, int32_t pi, int32_t c,
-                                          void* const* __restrict__ bufs, int32_t xcd_run,
+                                          Bufs bufs, int32_t xcd_run,
                                           Vec<S, CPLX ? 2 : 1>* lds, S ar, S ai, S br, S bi) {
   using TT = TypeTraits<S, CPLX>;
   using E = Vec<S, TT::NS>;
@@ -627,7 +638,7 @@ __device__ __forceinline__ void move_tile(const Piece* __restrict__ pieces, int3
 // The row walk of one workgroup for a fixed arithmetic mode.
 template <typename S, bool CPLX, int MODE, bool CONJ, int UL>
 __device__ __forceinline__ void walk_task(const Piece* __restrict__ pieces, int32_t pi, int32_t c,
-                                          void* const* __restrict__ bufs, const ItemParam* __restrict__ ip,
+                                          Bufs bufs, Items ip,
                                           int32_t allow_wide) {
   S ar = S(0), ai = S(0), br = S(0), bi = S(0);
   if constexpr (MODE != MODE_COPY) {
@@ -652,7 +663,7 @@ __device__ __forceinline__ void walk_task(const Piece* __restrict__ pieces, int3
 // The LDS tile of one workgroup for a fixed arithmetic mode.
 template <typename S, bool CPLX, int MODE, bool CONJ, int T>
 __device__ __forceinline__ void tile_task(const Piece* __restrict__ pieces, int32_t pi, int32_t c,
-                                          void* const* __restrict__ bufs, const ItemParam* __restrict__ ip,
+                                          Bufs bufs, Items ip,
                                           int32_t xcd_run, Vec<S, CPLX ? 2 : 1>* lds) {
   S ar = S(0), ai = S(0), br = S(0), bi = S(0);
   if constexpr (MODE != MODE_COPY) {
@@ -700,11 +711,12 @@ constexpr int units_per_lane() {
 // first task of a rectangle is in aux.
 template <typename S, bool CPLX, int KIND, int MODE, bool CONJ>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8)))
-costa_mover(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks, int32_t task_off,
-            void* const* __restrict__ bufs, const ItemParam* __restrict__ items, int32_t allow_wide,
-            int32_t xcd_run) {
+costa_mover(ArgTable, const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks, int32_t task_off,
+            const void* __restrict__ device_table, int32_t items_off, int32_t allow_wide, int32_t xcd_run) {
   using TT = TypeTraits<S, CPLX>;
   constexpr int UL = units_per_lane<KIND, MODE>();
+  const char COSTA_CONST* table = call_table(device_table);
+  const Bufs bufs = (Bufs)table;
   const int32_t b = task_off + xcd_order((int32_t)blockIdx.x, (int32_t)gridDim.x, xcd_run);
   const int32_t pi = tasks[b];
   const int32_t c = b - (UL == 1 ? pieces[pi].task0 : pieces[pi].aux);
@@ -719,7 +731,7 @@ costa_mover(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks,
       move_walk<S, CPLX, MODE_COPY, false, UL>(pieces, pi, c * (UL * kThreads), bufs, allow_wide, S(0), S(0), S(0),
                                                S(0));
   } else {
-    const ItemParam* ip = items + pieces[pi].item;
+    const Items ip = (Items)(table + items_off) + pieces[pi].item;
     if constexpr (MODE != MODE_ANY) {
       walk_task<S, CPLX, MODE, CONJ, UL>(pieces, pi, c, bufs, ip, allow_wide);
     } else {
@@ -734,14 +746,16 @@ costa_mover(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks,
 // as above.
 template <typename S, bool CPLX, int KIND, int MODE, bool CONJ, int T>
 __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(2, 8)))
-costa_tiles(const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks, int32_t task_off,
-            void* const* __restrict__ bufs, const ItemParam* __restrict__ items, int32_t xcd_run) {
+costa_tiles(ArgTable, const Piece* __restrict__ pieces, const int32_t* __restrict__ tasks, int32_t task_off,
+            const void* __restrict__ device_table, int32_t items_off, int32_t xcd_run) {
   using TT = TypeTraits<S, CPLX>;
   __shared__ Vec<S, TT::NS> lds[tile_lds_elems(TT::ES, T)];
+  const char COSTA_CONST* table = call_table(device_table);
+  const Bufs bufs = (Bufs)table;
   const int32_t b = task_off + xcd_order((int32_t)blockIdx.x, (int32_t)gridDim.x, xcd_run);
   const int32_t pi = tasks[b];
   const int32_t c = b - pieces[pi].task0;
-  const ItemParam* ip = items + pieces[pi].item;
+  const Items ip = (Items)(table + items_off) + pieces[pi].item;
   if constexpr (MODE != MODE_ANY) {
     tile_task<S, CPLX, MODE, CONJ, T>(pieces, pi, c, bufs, ip, xcd_run, lds);
   } else {
@@ -787,8 +801,9 @@ struct Launch {
   int64_t ntasks;
   const int32_t* wide;   // its wide task table (launches of row walks)
   int64_t nwide;
-  void* const* bufs;
-  const ItemParam* items;
+  const ArgTable& args;
+  const void* device_table;
+  int32_t items_off;
   int32_t allow_wide;
   int32_t xcd_run;
 };
@@ -841,16 +856,16 @@ hipError_t go_walks(const Launch& l) {
   constexpr bool WIDE = units_per_lane<KIND, MODE>() > 1;
   const int32_t* tasks = WIDE ? l.wide : l.tasks;
   return in_slices(WIDE ? l.nwide : l.ntasks, [&](unsigned n, int32_t off) {
-    hipLaunchKernelGGL((costa_mover<S, CPLX, KIND, MODE, CONJ>), dim3(n), dim3(kThreads), 0, l.stream, l.pieces, tasks,
-                       off, l.bufs, l.items, l.allow_wide, l.xcd_run);
+    hipLaunchKernelGGL((costa_mover<S, CPLX, KIND, MODE, CONJ>), dim3(n), dim3(kThreads), 0, l.stream, l.args, l.pieces,
+                       tasks, off, l.device_table, l.items_off, l.allow_wide, l.xcd_run);
   });
 }
 
 template <typename S, bool CPLX, int KIND, int MODE, bool CONJ, int T>
 hipError_t go_tiles(const Launch& l) {
   return in_slices(l.ntasks, [&](unsigned n, int32_t off) {
-    hipLaunchKernelGGL((costa_tiles<S, CPLX, KIND, MODE, CONJ, T>), dim3(n), dim3(T), 0, l.stream, l.pieces, l.tasks,
-                       off, l.bufs, l.items, l.xcd_run);
+    hipLaunchKernelGGL((costa_tiles<S, CPLX, KIND, MODE, CONJ, T>), dim3(n), dim3(T), 0, l.stream, l.args, l.pieces,
+                       l.tasks, off, l.device_table, l.items_off, l.xcd_run);
   });
 }
 
@@ -886,11 +901,13 @@ hipError_t launch_typed(MoverKind kind, const LaunchSpec& spec, const Launch& l)
 }  // namespace
 
 hipError_t launch_mover(MoverKind kind, costa_dtype dtype, const LaunchSpec& spec, const Piece* pieces,
-                        const int32_t* tasks, int64_t ntasks, const int32_t* wide, int64_t nwide, void* const* bufs,
-                        const ItemParam* items, int32_t allow_wide, int32_t xcd_run, hipStream_t stream) {
+                        const int32_t* tasks, int64_t ntasks, const int32_t* wide, int64_t nwide,
+                        const CallTable& table, int32_t allow_wide, int32_t xcd_run, hipStream_t stream) {
   if (ntasks <= 0) return hipSuccess;
   if (!spec.tile_lanes && nwide <= 0) return hipErrorInvalidValue;  // a launch of row walks has both tables
-  Launch l{stream, pieces, tasks, ntasks, wide, nwide, bufs, items, allow_wide, xcd_run};
+  static const ArgTable none{};
+  Launch l{stream, pieces, tasks, ntasks, wide, nwide, table.args ? *table.args : none,
+           table.args ? nullptr : table.device, table.items_off, allow_wide, xcd_run};
   switch (dtype) {
     case COSTA_R64: return launch_typed<double, false>(kind, spec, l);
     case COSTA_C128: return launch_typed<double, true>(kind, spec, l);
