@@ -73,6 +73,17 @@ struct Workspace {
   bool used = false;
 };
 
+// Memory that volume-matrix calls keep per device: a device buffer, and a
+// pinned host buffer that the kernels also read and write.  A call holds the
+// state's lock until its kernels have ended, so one of each serves every
+// stream and thread.
+struct VolumeScratch {
+  static constexpr size_t kBytes = (size_t)1 << 20;
+  unsigned char* dev = nullptr;
+  unsigned char* host = nullptr;
+  bool clean = false;  // the separable kernel's histograms and counter are zero
+};
+
 struct TimingRec {
   costa_kernel_kind kind;
   hipEvent_t start, stop;
@@ -86,6 +97,7 @@ struct State {
   std::map<std::string, std::unique_ptr<DevicePlan>> plans;
   std::map<std::string, std::unique_ptr<HostPlan>> host_plans;  // plan statistics without a device
   std::map<int, Workspace> ws;
+  std::map<int, VolumeScratch> volume;
   int timing = 0;  // COSTA_TIMING_MESSAGES, COSTA_TIMING_AS_CALLED or 0 (off)
   std::vector<TimingRec> pending;
   std::map<int, std::vector<hipEvent_t>> event_pool;  // per device: events are recorded on that device's streams
@@ -789,6 +801,123 @@ hipError_t upload(DevBuf& d, const T* src, size_t n, hipStream_t stream) {
   return hipMemcpyAsync(d.p, src, n * sizeof(T), hipMemcpyHostToDevice, stream);
 }
 
+// The current device's volume scratch, allocated by the first call.
+costa_status volume_scratch(State& S, VolumeScratch*& out) {
+  int device = 0;
+  HIP_OR_FAIL(hipGetDevice(&device));
+  VolumeScratch& v = S.volume[device];
+  if (!v.dev) HIP_OR_FAIL(hipMalloc(&v.dev, VolumeScratch::kBytes));
+  if (!v.host) HIP_OR_FAIL(hipHostMalloc(&v.host, VolumeScratch::kBytes, hipHostMallocDefault));
+  out = &v;
+  return COSTA_SUCCESS;
+}
+
+// Each rank's row and column class in A's grid (ca) and in op(B)'s (cb), -1
+// outside the grid (a rank map may leave ranks out); 2 P entries each.
+template <typename I>
+void rank_classes(const Layout& A, const Layout& B, bool tr, I* ca, I* cb) {
+  std::fill(ca, ca + (size_t)2 * A.nranks, (I)-1);
+  std::fill(cb, cb + (size_t)2 * A.nranks, (I)-1);
+  for (int32_t pr = 0; pr < A.prow; ++pr)
+    for (int32_t pc = 0; pc < A.pcol; ++pc) {
+      const int32_t r = A.rank_at(pr, pc);
+      ca[(size_t)2 * r] = (I)pr;
+      ca[(size_t)2 * r + 1] = (I)pc;
+    }
+  for (int32_t pr = 0; pr < B.prow; ++pr)
+    for (int32_t pc = 0; pc < B.pcol; ++pc) {
+      const int32_t r = B.rank_at(pr, pc);
+      cb[(size_t)2 * r] = (I)(tr ? pc : pr);
+      cb[(size_t)2 * r + 1] = (I)(tr ? pr : pc);
+    }
+}
+
+// Volume matrix of two block-cyclic layouts in one launch; `done` stays false
+// (and nothing has happened) where the layouts pass the kernel's limits.
+costa_status volume_dealt(const Layout& A, const Layout& B, bool tr, int64_t* V_host, hipStream_t stream,
+                          bool& done) {
+  const int32_t P = A.nranks;
+  // rows of op(B) are B's columns when it is transposed
+  struct Dim {
+    int64_t off, blk;
+    int32_t np, src, nblocks;
+  };
+  auto rows_of = [](const Layout& L) { return Dim{L.r0, L.mb, L.prow, L.rsrc, L.nbr}; };
+  auto cols_of = [](const Layout& L) { return Dim{L.c0, L.nb, L.pcol, L.csrc, L.nbc}; };
+  VolumeDealtArgs a{};
+  int64_t nhist = 0;
+  for (int d = 0; d < 2; ++d) {
+    const Dim da = d == 0 ? rows_of(A) : cols_of(A);
+    const Dim db = (d == 0) != tr ? rows_of(B) : cols_of(B);
+    if ((int64_t)da.nblocks + db.nblocks > INT32_MAX) return COSTA_SUCCESS;
+    const bool b_fine = db.nblocks >= da.nblocks;
+    const Dim &f = b_fine ? db : da, &c = b_fine ? da : db;
+    VolumeAxis& x = a.axis[d];
+    x.n = d == 0 ? A.nrows : A.ncols;
+    x.fine = VolumeSide{f.off, f.blk, f.np, f.src};
+    x.coarse = VolumeSide{c.off, c.blk, c.np, c.src};
+    x.nblocks = f.nblocks;
+    x.fine_is_b = b_fine ? 1 : 0;
+    x.nclass = da.np;
+    x.hist0 = (int32_t)nhist;
+    nhist += (int64_t)da.np * db.np;
+    if (nhist > kVolumeHistMax) return COSTA_SUCCESS;
+  }
+  if (P > kVolumeRanksMax) return COSTA_SUCCESS;
+  // (positions and block ends up to one block past the window, plus a source process)
+  a.narrow = 1;
+  for (const VolumeAxis& x : a.axis)
+    for (const VolumeSide& q : {x.fine, x.coarse})
+      if (q.off + x.n + 2 * q.blk + q.src > (int64_t)INT32_MAX) a.narrow = 0;
+  a.nhist = (int32_t)nhist;
+  a.P = P;
+  done = true;
+  State& S = state();
+  std::lock_guard<std::mutex> lock(S.mu);
+  VolumeScratch* vs = nullptr;
+  costa_status st = volume_scratch(S, vs);
+  if (st != COSTA_SUCCESS) return st;
+  if (!vs->clean) {
+    constexpr size_t n = (kVolumeHistMax + 1) * sizeof(unsigned long long);
+    std::memset(vs->host, 0, n);
+    HIP_OR_FAIL(hipMemcpyAsync(vs->dev, vs->host, n, hipMemcpyHostToDevice, stream));
+    HIP_OR_FAIL(hipStreamSynchronize(stream));
+  }
+  vs->clean = false;  // until this call's kernel has left them at zero
+  static_assert(sizeof(int64_t) * kVolumeRanksMax * kVolumeRanksMax <= VolumeScratch::kBytes, "V fits the pinned buffer");
+  rank_classes(A, B, tr, a.cls, a.cls + (size_t)2 * P);
+  a.hist = reinterpret_cast<unsigned long long*>(vs->dev);
+  a.V = reinterpret_cast<unsigned long long*>(vs->host);
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  int ev_device = 0;
+  if (S.timing && hipGetDevice(&ev_device) == hipSuccess) {
+    e0 = get_event(S, ev_device);
+    e1 = get_event(S, ev_device);
+  }
+  auto run = [&]() -> costa_status {
+    if (e0 && e1) HIP_OR_FAIL(hipEventRecord(e0, stream));
+    HIP_OR_FAIL(launch_volume_dealt(a, stream));
+    if (e0 && e1) {
+      HIP_OR_FAIL(hipEventRecord(e1, stream));
+      S.pending.push_back(TimingRec{COSTA_KERNEL_VOLUME, e0, e1,
+                                    ((int64_t)A.nbr + A.nbc + B.nbr + B.nbc) * 24, ev_device});
+      e0 = e1 = nullptr;
+    }
+    HIP_OR_FAIL(hipStreamSynchronize(stream));
+    return COSTA_SUCCESS;
+  };
+  st = run();
+  put_event(S, ev_device, e0);
+  put_event(S, ev_device, e1);
+  if (st != COSTA_SUCCESS) {
+    (void)hipStreamSynchronize(stream);  // the pinned buffer is the next call's too
+    return st;
+  }
+  vs->clean = true;
+  std::memcpy(V_host, vs->host, sizeof(int64_t) * (size_t)P * P);
+  return COSTA_SUCCESS;
+}
+
 }  // namespace
 }  // namespace costa
 
@@ -805,6 +934,11 @@ extern "C" costa_status costa_volume_matrix(costa_layout A_h, costa_layout B_h, 
     if (A->nranks != B->nranks) return fail(COSTA_ERROR_SHAPE_MISMATCH, "layouts of A and B have different P");
     const int32_t P = A->nranks;
     const size_t PP = (size_t)P * P;
+    if (A->block_cyclic && B->block_cyclic && A->nrows > 0 && A->ncols > 0) {
+      bool done = false;
+      const costa_status st = volume_dealt(*A, *B, tr, V_host, stream, done);
+      if (done) return st;
+    }
     std::memset(V_host, 0, sizeof(int64_t) * PP);
     std::vector<Interval> rows = overlay(A->rsplit, tr ? B->csplit : B->rsplit);
     std::vector<Interval> cols = overlay(A->csplit, tr ? B->rsplit : B->csplit);
@@ -815,8 +949,11 @@ extern "C" costa_status costa_volume_matrix(costa_layout A_h, costa_layout B_h, 
     std::lock_guard<std::mutex> lock(S.mu);
     // two block-cyclic layouts (with or without a rank map): the separable kernels
     const bool separable = A->block_cyclic && B->block_cyclic;
-    DevBuf d_rows, d_cols, d_oa, d_ob, d_v, d_hr, d_hc, d_ca, d_cb;
+    DevBuf d_rows, d_cols, d_v, d_hr, d_hc, d_ca, d_cb;
     std::vector<unsigned long long> zeros;
+    std::vector<unsigned char> all;
+    unsigned long long* d_V = nullptr;
+    unsigned char* V_stage = nullptr;  // pinned memory that takes V first, or null
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int ev_device = 0;
     if (S.timing && hipGetDevice(&ev_device) == hipSuccess) {
@@ -824,8 +961,9 @@ extern "C" costa_status costa_volume_matrix(costa_layout A_h, costa_layout B_h, 
       e1 = get_event(S, ev_device);
     }
     auto run = [&]() -> costa_status {
-      HIP_OR_FAIL(d_v.alloc(sizeof(int64_t) * PP));
       if (separable) {
+        HIP_OR_FAIL(d_v.alloc(sizeof(int64_t) * PP));
+        d_V = d_v.as<unsigned long long>();
         // classes of the covering blocks: process row/column of A's block and
         // of op(B)'s block (B's process column for the rows of op(B) when
         // transposed, and its process row for the columns)
@@ -840,21 +978,8 @@ extern "C" costa_status costa_volume_matrix(costa_layout A_h, costa_layout B_h, 
         }
         const size_t nh_r = (size_t)nrb * A->prow, nh_c = (size_t)ncb * A->pcol;
         zeros.assign(std::max(nh_r, nh_c), 0ull);
-        // each rank's row and column class in A's grid and in op(B)'s (-1
-        // outside the grid: a rank map may leave ranks out)
-        std::vector<int32_t> ca((size_t)2 * P, -1), cb((size_t)2 * P, -1);
-        for (int32_t pr = 0; pr < A->prow; ++pr)
-          for (int32_t pc = 0; pc < A->pcol; ++pc) {
-            const int32_t r = A->rank_at(pr, pc);
-            ca[(size_t)2 * r] = pr;
-            ca[(size_t)2 * r + 1] = pc;
-          }
-        for (int32_t pr = 0; pr < B->prow; ++pr)
-          for (int32_t pc = 0; pc < B->pcol; ++pc) {
-            const int32_t r = B->rank_at(pr, pc);
-            cb[(size_t)2 * r] = tr ? pc : pr;
-            cb[(size_t)2 * r + 1] = tr ? pr : pc;
-          }
+        std::vector<int32_t> ca((size_t)2 * P), cb((size_t)2 * P);
+        rank_classes(*A, *B, tr, ca.data(), cb.data());
         HIP_OR_FAIL(upload(d_rows, rows.data(), rows.size(), stream));
         HIP_OR_FAIL(upload(d_cols, cols.data(), cols.size(), stream));
         HIP_OR_FAIL(upload(d_hr, zeros.data(), nh_r, stream));
@@ -863,7 +988,7 @@ extern "C" costa_status costa_volume_matrix(costa_layout A_h, costa_layout B_h, 
         HIP_OR_FAIL(upload(d_cb, cb.data(), cb.size(), stream));
         SeparableArgs a{d_rows.as<Interval>(), (int32_t)rows.size(), d_cols.as<Interval>(), (int32_t)cols.size(),
                         nrb, A->prow, ncb, A->pcol, d_hr.as<unsigned long long>(), d_hc.as<unsigned long long>(),
-                        d_ca.as<int32_t>(), d_cb.as<int32_t>(), P, d_v.as<unsigned long long>()};
+                        d_ca.as<int32_t>(), d_cb.as<int32_t>(), P, d_V};
         if (e0) HIP_OR_FAIL(hipEventRecord(e0, stream));
         HIP_OR_FAIL(launch_volume_separable(a, stream));
       } else {
@@ -878,15 +1003,46 @@ extern "C" costa_status costa_volume_matrix(costa_layout A_h, costa_layout B_h, 
         };
         const std::vector<int32_t>& oa = owners(A, oa_tmp);
         const std::vector<int32_t>& ob = owners(B, ob_tmp);
-        zeros.assign(PP, 0ull);
-        HIP_OR_FAIL(upload(d_rows, rows.data(), rows.size(), stream));
-        HIP_OR_FAIL(upload(d_cols, cols.data(), cols.size(), stream));
-        HIP_OR_FAIL(upload(d_oa, oa.data(), oa.size(), stream));
-        HIP_OR_FAIL(upload(d_ob, ob.data(), ob.size(), stream));
-        HIP_OR_FAIL(hipMemcpyAsync(d_v.p, zeros.data(), sizeof(int64_t) * PP, hipMemcpyHostToDevice, stream));
-        VolumeArgs a{d_rows.as<Interval>(), (int32_t)rows.size(), d_cols.as<Interval>(), (int32_t)cols.size(),
-                     d_oa.as<int32_t>(), A->nbc, d_ob.as<int32_t>(), B->nbc, tr ? 1 : 0, P,
-                     d_v.as<unsigned long long>()};
+        // one upload of everything the kernel reads and of V's zeros
+        struct Part {
+          const void* src;
+          size_t bytes, at;
+        } part[5] = {{rows.data(), rows.size() * sizeof(Interval), 0},
+                     {cols.data(), cols.size() * sizeof(Interval), 0},
+                     {oa.data(), oa.size() * sizeof(int32_t), 0},
+                     {ob.data(), ob.size() * sizeof(int32_t), 0},
+                     {nullptr, sizeof(int64_t) * PP, 0}};
+        size_t total = 0;
+        for (Part& q : part) {
+          q.at = total;
+          total += (q.bytes + 255) / 256 * 256;
+        }
+        unsigned char* dev = nullptr;
+        unsigned char* host = nullptr;
+        if (total <= VolumeScratch::kBytes) {
+          VolumeScratch* vs = nullptr;
+          costa_status sst = volume_scratch(S, vs);
+          if (sst != COSTA_SUCCESS) return sst;
+          vs->clean = false;  // the device buffer also holds the separable kernel's histograms
+          dev = vs->dev;
+          host = vs->host;
+        } else {
+          HIP_OR_FAIL(d_v.alloc(total));
+          all.resize(total);
+          dev = d_v.as<unsigned char>();
+          host = all.data();
+        }
+        for (const Part& q : part) {
+          if (q.src) std::memcpy(host + q.at, q.src, q.bytes);
+          else std::memset(host + q.at, 0, q.bytes);
+        }
+        HIP_OR_FAIL(hipMemcpyAsync(dev, host, total, hipMemcpyHostToDevice, stream));
+        d_V = reinterpret_cast<unsigned long long*>(dev + part[4].at);
+        if (host != all.data()) V_stage = host + part[4].at;
+        VolumeArgs a{reinterpret_cast<const Interval*>(dev), (int32_t)rows.size(),
+                     reinterpret_cast<const Interval*>(dev + part[1].at), (int32_t)cols.size(),
+                     reinterpret_cast<const int32_t*>(dev + part[2].at), A->nbc,
+                     reinterpret_cast<const int32_t*>(dev + part[3].at), B->nbc, tr ? 1 : 0, P, d_V};
         if (e0) HIP_OR_FAIL(hipEventRecord(e0, stream));
         HIP_OR_FAIL(launch_volume(a, stream));
       }
@@ -896,8 +1052,10 @@ extern "C" costa_status costa_volume_matrix(costa_layout A_h, costa_layout B_h, 
             TimingRec{COSTA_KERNEL_VOLUME, e0, e1, (int64_t)(rows.size() + cols.size()) * 24, ev_device});
         e0 = e1 = nullptr;
       }
-      HIP_OR_FAIL(hipMemcpyAsync(V_host, d_v.p, sizeof(int64_t) * PP, hipMemcpyDeviceToHost, stream));
+      HIP_OR_FAIL(hipMemcpyAsync(V_stage ? (void*)V_stage : (void*)V_host, d_V, sizeof(int64_t) * PP,
+                                 hipMemcpyDeviceToHost, stream));
       HIP_OR_FAIL(hipStreamSynchronize(stream));
+      if (V_stage) std::memcpy(V_host, V_stage, sizeof(int64_t) * PP);
       return COSTA_SUCCESS;
     };
     costa_status st = run();
@@ -1177,6 +1335,11 @@ extern "C" costa_status costa_finalize(void) {
         if (kv.second.last_use) (void)hipEventDestroy(kv.second.last_use);
       }
       S.ws.clear();
+      for (auto& kv : S.volume) {
+        if (kv.second.dev) (void)hipFree(kv.second.dev);
+        if (kv.second.host) (void)hipHostFree(kv.second.host);
+      }
+      S.volume.clear();
       for (auto& kv : S.event_pool)
         for (hipEvent_t e : kv.second) (void)hipEventDestroy(e);
       S.event_pool.clear();

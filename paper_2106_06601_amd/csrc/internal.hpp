@@ -353,7 +353,38 @@ struct VolumeArgs {
 };
 hipError_t launch_volume(const VolumeArgs& a, hipStream_t stream);
 
-// Separable volume of two block-cyclic layouts: per-dimension histograms of
+// Separable volume of two block-cyclic layouts in one launch.  A dimension is
+// the rows or the columns of A; each side deals it in blocks of `blk` over
+// `np` processes from process `src`, and the window's element i is element
+// off + i of the dealt dimension.
+struct VolumeSide {
+  int64_t off, blk;
+  int32_t np, src;
+};
+struct VolumeAxis {
+  int64_t n;            // elements
+  VolumeSide fine;      // the side with more blocks: the kernel's threads take one of them each
+  VolumeSide coarse;
+  int32_t nblocks;      // blocks of the fine side that meet the window
+  int32_t fine_is_b;
+  int32_t nclass;       // processes of A's side (the histogram's row length)
+  int32_t hist0;        // first entry of the axis in the histogram
+};
+constexpr int32_t kVolumeHistMax = 4096;    // entries (32 KiB of LDS)
+constexpr int32_t kVolumeRanksMax = 256;    // ranks (512 KiB of V, 2 KiB of classes among the arguments)
+struct VolumeDealtArgs {
+  VolumeAxis axis[2];           // rows, columns of A
+  int32_t nhist;                // entries of both histograms
+  int32_t P;
+  int32_t narrow;               // both axes' positions fit 32 bits
+  unsigned long long* hist;     // nhist entries, zero between launches, then a counter of workgroups (zero too)
+  unsigned long long* V;        // P x P
+  int16_t cls[4 * kVolumeRanksMax];  // clsA then clsB (see SeparableArgs), 2 P entries each
+};
+hipError_t launch_volume_dealt(const VolumeDealtArgs& a, hipStream_t stream);
+
+// Separable volume of two block-cyclic layouts whose histograms or ranks pass
+// those limits: per-dimension histograms of
 // the overlay intervals over (class in B, class in A) -- Interval::a and ::b
 // hold those classes here -- then V[s][t] as the product of a row and a
 // column histogram entry.

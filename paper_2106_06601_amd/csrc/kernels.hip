@@ -808,6 +808,88 @@ struct Launch {
   int32_t xcd_run;
 };
 
+// Separable volume in one launch.  Thread per block of the finer side: it
+// walks the coarse blocks that its block meets (at most two unless the sides'
+// block sizes are alike) and adds each overlap to an LDS histogram by
+// (process in op(B), process in A).  Up to kVolumeOneGroup blocks one
+// workgroup does both axes; otherwise the workgroups flush their histograms
+// with device-scope atomics, and the last one to finish reads the sums and
+// leaves them and its counter at zero for the next launch.  Then V[s][t] =
+// rows * columns.  Bound by latency: the launch, V written to host memory, the
+// host's wait.  Measured on MI355X, 10^5 x 10^5 over 10 x 10 ranks, blocks of
+// 30 into 10^4: two launches among six uploads and seven allocations 140 us a
+// call, this one 30 (the kernel 9.1; 13.1 with the classes read row by row,
+// 16.7 with 64-bit divisions and several workgroups as well); blocks of 2,
+// 50,000 an axis, 20 us in the kernel against 116.
+constexpr int kVolumeThreads = 1024;
+constexpr int kVolumeOneGroup = 16384;
+
+template <typename I>
+__device__ __forceinline__ void count_overlaps(const VolumeAxis& x, unsigned long long* h, int32_t first,
+                                               int32_t step) {
+  const I off = (I)x.fine.off, blk = (I)x.fine.blk, coff = (I)x.coarse.off, cblk = (I)x.coarse.blk, n = (I)x.n;
+  const I fnp = (I)x.fine.np, fsrc = (I)x.fine.src, cnp = (I)x.coarse.np, csrc = (I)x.coarse.src;
+  const I k0 = off / blk;  // the window's first block in the dealt dimension
+  for (int32_t k = first; k < x.nblocks; k += step) {
+    const I b = k0 + (I)k;
+    I i = max(off, b * blk) - off;  // in the window
+    const I end = min(off + n, (b + 1) * blk) - off;
+    const int32_t pf = (int32_t)((b + fsrc) % fnp);
+    while (i < end) {
+      const I cb = (coff + i) / cblk;
+      const I stop = min(end, (cb + 1) * cblk - coff);
+      const int32_t pc = (int32_t)((cb + csrc) % cnp);
+      atomicAdd(&h[x.fine_is_b ? pf * x.nclass + pc : pc * x.nclass + pf], (unsigned long long)(stop - i));
+      i = stop;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(kVolumeThreads) costa_volume_dealt(VolumeDealtArgs a) {
+  __shared__ unsigned long long h[kVolumeHistMax];
+  __shared__ int16_t cls[4 * kVolumeRanksMax];
+  __shared__ int32_t last;
+  const int32_t tid = threadIdx.x;
+  const bool one = gridDim.x == 1;  // (then blockIdx.y is 0 alone)
+  // all of the arguments' classes at once: read row by row below, each would
+  // wait a memory round trip
+  if (tid < 4 * a.P) cls[tid] = a.cls[tid];
+  static_assert(4 * kVolumeRanksMax <= kVolumeThreads, "a class a lane");
+  for (int32_t i = tid; i < a.nhist; i += kVolumeThreads) h[i] = 0ull;
+  __syncthreads();
+  for (int32_t d = one ? 0 : blockIdx.y; d <= (one ? 1 : (int32_t)blockIdx.y); ++d) {
+    const VolumeAxis& x = a.axis[d];
+    const int32_t first = blockIdx.x * kVolumeThreads + tid, step = gridDim.x * kVolumeThreads;
+    if (a.narrow) count_overlaps<uint32_t>(x, h + x.hist0, first, step);
+    else count_overlaps<uint64_t>(x, h + x.hist0, first, step);
+  }
+  __syncthreads();
+  if (!one) {
+    for (int32_t i = tid; i < a.nhist; i += kVolumeThreads)
+      if (h[i]) atomicAdd(&a.hist[i], h[i]);
+    __threadfence();  // the sums are in device memory before this workgroup is counted
+    __syncthreads();
+    if (tid == 0) last = atomicAdd(&a.hist[a.nhist], 1ull) == (unsigned long long)gridDim.x * gridDim.y - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    for (int32_t i = tid; i < a.nhist; i += kVolumeThreads) h[i] = atomicExch(&a.hist[i], 0ull);
+    if (tid == 0) a.hist[a.nhist] = 0ull;
+    __syncthreads();
+  }
+  // a wave per row of V
+  const int32_t lane = tid % 64;
+  const unsigned long long *hr = h + a.axis[0].hist0, *hc = h + a.axis[1].hist0;
+  for (int32_t s = tid / 64; s < a.P; s += kVolumeThreads / 64) {
+    const int32_t rb = cls[2 * (a.P + s)], cb = cls[2 * (a.P + s) + 1];
+    for (int32_t t = lane; t < a.P; t += 64) {
+      const int32_t ra = cls[2 * t], ca = cls[2 * t + 1];
+      a.V[(int64_t)s * a.P + t] =
+          (ra < 0 || rb < 0) ? 0ull : hr[rb * a.axis[0].nclass + ra] * hc[cb * a.axis[1].nclass + ca];
+    }
+  }
+}
+
 // Separable volume, step 1: histogram of overlay interval lengths by (class
 // of the covering block in op(B), class of the covering block in A), for the
 // rows (blockIdx.y == 0) and the columns (blockIdx.y == 1).
@@ -915,6 +997,16 @@ hipError_t launch_mover(MoverKind kind, costa_dtype dtype, const LaunchSpec& spe
     case COSTA_C64: return launch_typed<float, true>(kind, spec, l);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_volume_dealt(const VolumeDealtArgs& a, hipStream_t stream) {
+  const int32_t nmax = a.axis[0].nblocks > a.axis[1].nblocks ? a.axis[0].nblocks : a.axis[1].nblocks;
+  // four blocks a thread, at most 64 workgroups an axis: every workgroup flushes a histogram
+  unsigned gx = (unsigned)((nmax + 4 * kVolumeThreads - 1) / (4 * kVolumeThreads));
+  gx = gx < 2 ? 2 : gx > 64 ? 64 : gx;
+  const bool one = (int64_t)a.axis[0].nblocks + a.axis[1].nblocks <= kVolumeOneGroup;
+  hipLaunchKernelGGL(costa_volume_dealt, one ? dim3(1, 1) : dim3(gx, 2), dim3(kVolumeThreads), 0, stream, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_volume_separable(const SeparableArgs& a, hipStream_t stream) {
