@@ -1084,21 +1084,29 @@ static_assert(kNoallocTableBytes % 256 == 0 && kNoallocTableBytes < kNoallocByte
 // the address hipGetSymbolAddress returns on each device.
 static __device__ __align__(256) unsigned char scratch[kNoallocBytes];
 
-// A plan of the no-allocation path, with the offsets of its tables in the
-// scratch array; the message form is planned for messages of at most
-// kNoallocMessageBytes per wave.
+// A plan of the no-allocation path; the message form is planned for messages
+// of at most kNoallocMessageBytes per wave.
 struct NoallocPlan {
-  HostPlan host;
+  HostPlan host;                      // (its rectangles and task tables moved to `tables`)
+  std::vector<unsigned char> tables;  // what the scratch array holds of it: rectangles, tasks, wide tasks
   uint64_t serial = 0;  // tells plans apart when one is rebuilt at a freed address
-  bool accepted = false;  // direct form: the message form's tables fit as well
+  // offsets in the plan's part of the scratch array; the call table follows
+  // the tables
   size_t off_tasks = 0, off_wide = 0, off_table = 0, end = 0;
+  bool accepted = false;  // direct form: the message form's tables fit as well
 };
 
 // What one device's scratch array holds.
 struct NoallocDevice {
-  unsigned char* base = nullptr;     // address of `scratch` on the device
-  uint64_t resident = 0;             // serial of the plan whose tables it holds (0: none)
-  std::vector<unsigned char> table;  // the call table it holds
+  struct Resident {
+    size_t at;                         // start of the plan's part
+    std::vector<unsigned char> table;  // the call table it holds (calls whose table is no kernel argument)
+  };
+  unsigned char* base = nullptr;  // address of `scratch` on the device
+  // the plans whose tables it holds, by serial: parts are handed out one
+  // after another, and start over when the next one does not fit
+  std::map<uint64_t, Resident> resident;
+  size_t used = 0;
 };
 
 struct NoallocState {
@@ -1113,32 +1121,6 @@ NoallocState& noalloc_state() {
 }
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
-
-// The cached plan of one form of a no-allocation call, built if need be (host
-// memory only; no device call).
-NoallocPlan& noalloc_form(Form form, costa_dtype dt, const std::vector<ItemDesc>& items,
-                          const std::vector<int32_t>& sig) {
-  NoallocState& N = noalloc_state();
-  const int es = elem_size(dt);
-  std::string key = plan_key(-1, form, es, items, sig, kNoallocMessageBytes);
-  auto it = N.plans.find(key);
-  if (it == N.plans.end()) {
-    if (N.plans.size() >= 64) N.plans.clear();
-    std::unique_ptr<NoallocPlan> np(new NoallocPlan());
-    build_plan(items, sig, make_config(es, form),
-               [](int64_t need) { return std::min<int64_t>(need, (int64_t)kNoallocMessageBytes); }, np->host);
-    const HostPlan& hp = np->host;
-    const int32_t P = items.empty() ? 0 : items[0].A->nranks;
-    const size_t nbufs = (size_t)2 * items.size() * P + 1;
-    np->off_tasks = align256(hp.pieces.size() * sizeof(Piece));
-    np->off_wide = np->off_tasks + align256(hp.tasks.size() * sizeof(int32_t));
-    np->off_table = np->off_wide + align256(hp.wide_tasks.size() * sizeof(int32_t));
-    np->end = np->off_table + (nbufs * sizeof(void*) + 63) / 64 * 64 + items.size() * sizeof(ItemParam);
-    np->serial = N.next_serial++;
-    it = N.plans.emplace(key, std::move(np)).first;
-  }
-  return *it->second;
-}
 
 // Whether the message form's tables would fit the scratch array for sure,
 // from the direct plan's rectangles: at most two for each (a rectangle larger
@@ -1157,6 +1139,44 @@ bool message_tables_fit(const NoallocPlan& dp, int es) {
          kNoallocTableBytes;
 }
 
+// The cached plan of one form of a no-allocation call, built if need be (host
+// memory only; no device call).
+NoallocPlan& noalloc_form(Form form, costa_dtype dt, const std::vector<ItemDesc>& items,
+                          const std::vector<int32_t>& sig) {
+  NoallocState& N = noalloc_state();
+  const int es = elem_size(dt);
+  std::string key = plan_key(-1, form, es, items, sig, kNoallocMessageBytes);
+  auto it = N.plans.find(key);
+  if (it == N.plans.end()) {
+    if (N.plans.size() >= 64) N.plans.clear();
+    std::unique_ptr<NoallocPlan> np(new NoallocPlan());
+    build_plan(items, sig, make_config(es, form),
+               [](int64_t need) { return std::min<int64_t>(need, (int64_t)kNoallocMessageBytes); }, np->host);
+    HostPlan& hp = np->host;
+    const int32_t P = items.empty() ? 0 : items[0].A->nranks;
+    const size_t nbufs = (size_t)2 * items.size() * P + 1;
+    const size_t pieces = hp.pieces.size() * sizeof(Piece), tasks = hp.tasks.size() * sizeof(int32_t),
+                 wide = hp.wide_tasks.size() * sizeof(int32_t);
+    np->off_tasks = align256(pieces);
+    np->off_wide = np->off_tasks + align256(tasks);
+    np->off_table = np->off_wide + align256(wide);
+    np->end = np->off_table + (nbufs * sizeof(void*) + 63) / 64 * 64 + items.size() * sizeof(ItemParam);
+    np->serial = N.next_serial++;
+    if (np->end <= kNoallocTableBytes) {
+      np->accepted = form == FORM_DIRECT && message_tables_fit(*np, es);
+      np->tables.assign(np->off_table, 0);
+      if (pieces) std::memcpy(np->tables.data(), hp.pieces.data(), pieces);
+      if (tasks) std::memcpy(np->tables.data() + np->off_tasks, hp.tasks.data(), tasks);
+      if (wide) std::memcpy(np->tables.data() + np->off_wide, hp.wide_tasks.data(), wide);
+    }
+    std::vector<Piece>().swap(hp.pieces);
+    std::vector<int32_t>().swap(hp.tasks);
+    std::vector<int32_t>().swap(hp.wide_tasks);
+    it = N.plans.emplace(key, std::move(np)).first;
+  }
+  return *it->second;
+}
+
 // The plan of a no-allocation call: the direct form where the caller's
 // buffers allow it (`direct`) and its tables fit.  What the entry point
 // accepts is decided by the message form's tables, which are planned only
@@ -1166,10 +1186,7 @@ costa_status noalloc_plan(costa_dtype dt, const std::vector<ItemDesc>& items, co
   if (direct) {
     NoallocPlan& dp = noalloc_form(FORM_DIRECT, dt, items, sig);
     out = &dp;
-    if (dp.end <= kNoallocTableBytes && (dp.accepted || message_tables_fit(dp, elem_size(dt)))) {
-      dp.accepted = true;
-      return COSTA_SUCCESS;
-    }
+    if (dp.accepted) return COSTA_SUCCESS;
   }
   NoallocPlan& np = noalloc_form(FORM_MESSAGES, dt, items, sig);
   if (np.end > kNoallocTableBytes)
@@ -1235,22 +1252,22 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
     if (st != COSTA_SUCCESS) return st;
     const HostPlan& hp = np->host;
     unsigned char* base = dev->base;
-    // the plan's tables, unless the scratch holds them already (copies from
+    // the plan's tables, unless the scratch holds them already (a copy from
     // pageable host memory: the host data has been taken when the call returns)
-    if (dev->resident != np->serial) {
-      dev->resident = 0;
-      dev->table.clear();
-      if (!hp.pieces.empty())
-        HIP_OR_FAIL(hipMemcpyAsync(base, hp.pieces.data(), hp.pieces.size() * sizeof(Piece), hipMemcpyHostToDevice,
+    auto res = dev->resident.find(np->serial);
+    if (res == dev->resident.end()) {
+      if (dev->used + align256(np->end) > kNoallocTableBytes) {
+        dev->resident.clear();
+        dev->used = 0;
+      }
+      if (!np->tables.empty())
+        HIP_OR_FAIL(hipMemcpyAsync(base + dev->used, np->tables.data(), np->tables.size(), hipMemcpyHostToDevice,
                                    stream));
-      if (!hp.tasks.empty())
-        HIP_OR_FAIL(hipMemcpyAsync(base + np->off_tasks, hp.tasks.data(), hp.tasks.size() * sizeof(int32_t),
-                                   hipMemcpyHostToDevice, stream));
-      if (!hp.wide_tasks.empty())
-        HIP_OR_FAIL(hipMemcpyAsync(base + np->off_wide, hp.wide_tasks.data(), hp.wide_tasks.size() * sizeof(int32_t),
-                                   hipMemcpyHostToDevice, stream));
-      dev->resident = np->serial;
+      res = dev->resident.emplace(np->serial, NoallocDevice::Resident{dev->used, {}}).first;
+      dev->used += align256(np->end);
     }
+    NoallocDevice::Resident& here = res->second;
+    unsigned char* part = base + here.at;
     std::vector<unsigned char> table;
     std::vector<char> reads_a;
     bool aligned = true;
@@ -1261,17 +1278,17 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
       std::memcpy(args.bytes, table.data(), table.size());
       ct.args = &args;
     } else {
-      if (table != dev->table) {
-        dev->table.clear();
-        HIP_OR_FAIL(hipMemcpyAsync(base + np->off_table, table.data(), table.size(), hipMemcpyHostToDevice, stream));
-        dev->table = table;
+      if (table != here.table) {
+        here.table.clear();
+        HIP_OR_FAIL(hipMemcpyAsync(part + np->off_table, table.data(), table.size(), hipMemcpyHostToDevice, stream));
+        here.table = table;
       }
-      ct.device = base + np->off_table;
+      ct.device = part + np->off_table;
     }
     const ItemParam* ipar = reinterpret_cast<const ItemParam*>(table.data() + ptr_bytes);
-    const DeviceTables tabs{reinterpret_cast<const Piece*>(base),
-                            reinterpret_cast<const int32_t*>(base + np->off_tasks),
-                            reinterpret_cast<const int32_t*>(base + np->off_wide)};
+    const DeviceTables tabs{reinterpret_cast<const Piece*>(part),
+                            reinterpret_cast<const int32_t*>(part + np->off_tasks),
+                            reinterpret_cast<const int32_t*>(part + np->off_wide)};
     // no timing events on this path (creating one may allocate)
     return launch_plan(S, dtype, hp, tabs, ipar, n, reads_a, aligned, ct, stream, false);
   });
@@ -1327,8 +1344,8 @@ extern "C" costa_status costa_finalize(void) {
       S.host_plans.clear();
       N.plans.clear();
       for (auto& kv : N.devices) {  // the scratch arrays stay (static); what they hold is forgotten
-        kv.second.resident = 0;
-        kv.second.table.clear();
+        kv.second.resident.clear();
+        kv.second.used = 0;
       }
       for (auto& kv : S.ws) {
         if (kv.second.ptr) (void)hipFree(kv.second.ptr);

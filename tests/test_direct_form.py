@@ -224,3 +224,27 @@ def test_overlapping_buffers_take_the_message_form(entry):
                                                        B_local=bufs)])
     torch.cuda.synchronize()
     assert torch.equal(bufs[0], before[1]) and torch.equal(bufs[1], before[0])
+
+
+@pytest.mark.gpu
+def test_noalloc_plans_share_the_table_area():
+    """Twenty plans of about 1 MB of tables take turns, twice: the later ones
+    displace the earlier ones in the 16 MiB table area, and every call finds
+    its own."""
+    print("noalloc: 20 plans in turn", flush=True)
+    calls = []
+    for k in range(20):
+        A, B = BC(1024, 1000 + k, 24, 8, 2, 2, "row", "col"), BC(1024, 1000 + k, 8, 16, 2, 2, "col", "col")
+        LA, LB = C.layout_from_spec(A), C.layout_from_spec(B)
+        b = [torch.rand(LB.local_elems(r), dtype=torch.float64, device="cuda") for r in range(4)]
+        a = [torch.zeros(LA.local_elems(r), dtype=torch.float64, device="cuda") for r in range(4)]
+        want = [torch.zeros_like(t) for t in a]
+        C.costa_transform("f64", "N", 1.0, 0.0, LA, want, LB, b)
+        calls.append((dict(op="N", alpha=1.0, beta=0.0, A=LA, A_local=a, B=LB, B_local=b), a, want))
+    for _ in range(2):
+        for d, a, want in calls:
+            for t in a:
+                t.zero_()
+            C.costa_transform_batched_noalloc("f64", [d])
+            torch.cuda.synchronize()
+            assert all(torch.equal(x, y) for x, y in zip(a, want))
