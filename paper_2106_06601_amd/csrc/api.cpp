@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cstring>
+#include <iterator>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -1094,19 +1095,49 @@ struct NoallocPlan {
   // the tables
   size_t off_tasks = 0, off_wide = 0, off_table = 0, end = 0;
   bool accepted = false;  // direct form: the message form's tables fit as well
+  bool captured = false;  // a graph holds a copy from `tables`: the plan stays in the cache
 };
 
 // What one device's scratch array holds.
 struct NoallocDevice {
   struct Resident {
-    size_t at;                         // start of the plan's part
+    size_t at, end;                    // the plan's part
+    bool loaded = false;               // its tables are there (a copy that was only captured has not run yet)
+    bool held = false;                 // a captured call reads it on every replay
     std::vector<unsigned char> table;  // the call table it holds (calls whose table is no kernel argument)
   };
   unsigned char* base = nullptr;  // address of `scratch` on the device
   // the plans whose tables it holds, by serial: parts are handed out one
-  // after another, and start over when the next one does not fit
+  // after another, and start over when the next one does not fit.  Parts that
+  // captured calls read are passed over, and given up only for a plan that
+  // does not fit beside them.
   std::map<uint64_t, Resident> resident;
   size_t used = 0;
+
+  // A part of `size` bytes (at most kNoallocTableBytes, a multiple of 256).
+  size_t place(size_t size) {
+    for (int pass = 0; pass < 3; ++pass) {
+      if (pass > 0) {
+        for (auto it = resident.begin(); it != resident.end();)
+          it = pass == 1 && it->second.held ? std::next(it) : resident.erase(it);
+        used = 0;
+      }
+      size_t at = used;
+      for (bool moved = true; moved;) {
+        moved = false;
+        for (const auto& kv : resident)
+          if (at < kv.second.end && kv.second.at < at + size) {
+            at = kv.second.end;
+            moved = true;
+          }
+      }
+      if (at + size <= kNoallocTableBytes) {
+        used = at + size;
+        return at;
+      }
+    }
+    return 0;
+  }
 };
 
 struct NoallocState {
@@ -1148,7 +1179,8 @@ NoallocPlan& noalloc_form(Form form, costa_dtype dt, const std::vector<ItemDesc>
   std::string key = plan_key(-1, form, es, items, sig, kNoallocMessageBytes);
   auto it = N.plans.find(key);
   if (it == N.plans.end()) {
-    if (N.plans.size() >= 64) N.plans.clear();
+    if (N.plans.size() >= 64)
+      for (auto p = N.plans.begin(); p != N.plans.end();) p = p->second->captured ? std::next(p) : N.plans.erase(p);
     std::unique_ptr<NoallocPlan> np(new NoallocPlan());
     build_plan(items, sig, make_config(es, form),
                [](int64_t need) { return std::min<int64_t>(need, (int64_t)kNoallocMessageBytes); }, np->host);
@@ -1252,21 +1284,24 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
     if (st != COSTA_SUCCESS) return st;
     const HostPlan& hp = np->host;
     unsigned char* base = dev->base;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIP_OR_FAIL(hipStreamIsCapturing(stream, &capture));
+    const bool capturing = capture == hipStreamCaptureStatusActive;
     // the plan's tables, unless the scratch holds them already (a copy from
-    // pageable host memory: the host data has been taken when the call returns)
+    // pageable host memory: the host data has been taken when the call returns,
+    // or is read by the graph's copy on every replay)
     auto res = dev->resident.find(np->serial);
     if (res == dev->resident.end()) {
-      if (dev->used + align256(np->end) > kNoallocTableBytes) {
-        dev->resident.clear();
-        dev->used = 0;
-      }
-      if (!np->tables.empty())
-        HIP_OR_FAIL(hipMemcpyAsync(base + dev->used, np->tables.data(), np->tables.size(), hipMemcpyHostToDevice,
-                                   stream));
-      res = dev->resident.emplace(np->serial, NoallocDevice::Resident{dev->used, {}}).first;
-      dev->used += align256(np->end);
+      const size_t size = align256(np->end), at = dev->place(size);
+      res = dev->resident.emplace(np->serial, NoallocDevice::Resident{at, at + size}).first;
     }
     NoallocDevice::Resident& here = res->second;
+    if (!here.loaded) {
+      if (!np->tables.empty())
+        HIP_OR_FAIL(hipMemcpyAsync(base + here.at, np->tables.data(), np->tables.size(), hipMemcpyHostToDevice, stream));
+      here.loaded = !capturing;
+    }
+    if (capturing) here.held = np->captured = true;
     unsigned char* part = base + here.at;
     std::vector<unsigned char> table;
     std::vector<char> reads_a;
@@ -1279,9 +1314,11 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
       ct.args = &args;
     } else {
       if (table != here.table) {
-        here.table.clear();
-        HIP_OR_FAIL(hipMemcpyAsync(part + np->off_table, table.data(), table.size(), hipMemcpyHostToDevice, stream));
-        here.table = table;
+        here.table = table;  // (kept: a captured copy reads it on every replay)
+        const hipError_t e = hipMemcpyAsync(part + np->off_table, here.table.data(), table.size(),
+                                            hipMemcpyHostToDevice, stream);
+        if (e != hipSuccess) here.table.clear();
+        HIP_OR_FAIL(e);
       }
       ct.device = part + np->off_table;
     }

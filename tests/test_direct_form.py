@@ -248,3 +248,33 @@ def test_noalloc_plans_share_the_table_area():
             C.costa_transform_batched_noalloc("f64", [d])
             torch.cuda.synchronize()
             assert all(torch.equal(x, y) for x, y in zip(a, want))
+
+
+@pytest.mark.gpu
+def test_captured_noalloc_call_keeps_its_tables():
+    """A captured call replays right after other plans have taken turns in the
+    rest of the table area (20 of about 1 MB each)."""
+    print("noalloc: captured call, 20 plans between its replays", flush=True)
+    LA, LB = C.layout_from_spec(BC(700, 900, 24, 8, 2, 2, "row", "col")), \
+        C.layout_from_spec(BC(700, 900, 8, 16, 2, 2, "col", "col"))
+    b = [torch.rand(LB.local_elems(r), dtype=torch.float64, device="cuda") for r in range(4)]
+    a = [torch.zeros(LA.local_elems(r), dtype=torch.float64, device="cuda") for r in range(4)]
+    want = [torch.zeros_like(t) for t in a]
+    C.costa_transform("f64", "N", 1.0, 0.0, LA, want, LB, b)
+    d = dict(op="N", alpha=1.0, beta=0.0, A=LA, A_local=a, B=LB, B_local=b)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        C.costa_transform_batched_noalloc("f64", [d])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        C.costa_transform_batched_noalloc("f64", [d])
+    for _ in range(2):
+        test_noalloc_plans_share_the_table_area()
+        for t in a:
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(a, want))
