@@ -709,6 +709,30 @@ LaunchRange add_launch(HostPlan& hp, std::vector<Piece>& ps, int es, int32_t nit
   return lr;
 }
 
+// A rectangle one element wide whose source is contiguous (a block column cut
+// off by the other layout's splits) runs along y on its own and is planned as
+// a row walk of single elements.  Where a launch of tiles has no other row
+// walks, these become tiles too (the same elements; a tile of width one), so
+// that the call is one launch: on their own they leave the chip nearly empty
+// and the lines of A that they share with the tiles beside them are fetched
+// again.  Measured on MI355X: ragged float32 7001 x 4999, accumulated, 165
+// workgroups of columns after its tiles, 124.0 -> 117.1 us a call; a drawn
+// transpose 37.0 -> 30.8.
+void join_columns(std::vector<Piece>& ps, int es) {
+  bool tiles = false, columns = false;
+  for (const Piece& p : ps) {
+    if (p.flags & PIECE_TRANSPOSE) tiles = true;
+    else if (p.nx == 1 && (p.ny == 1 || p.src_ld == 1)) columns = true;
+    else return;
+  }
+  if (!tiles || !columns) return;
+  for (Piece& p : ps) {
+    if (p.flags & PIECE_TRANSPOSE) continue;
+    p.flags = PIECE_TRANSPOSE;
+    finish_piece(p, es);
+  }
+}
+
 #ifndef COSTA_PACK_BY_SOURCE
 #define COSTA_PACK_BY_SOURCE 1
 #endif
@@ -722,6 +746,7 @@ std::vector<LaunchRange> add_launches(HostPlan& hp, std::vector<Piece>& ps, int 
   if (ps.empty()) return out;
   std::vector<Piece> tiles, walks;
   size_t ntiles = 0;
+  if (small_tiles) join_columns(ps, es);
   for (const Piece& p : ps) ntiles += (p.flags & PIECE_TRANSPOSE) ? 1 : 0;
   if (ntiles > 0 && ntiles < ps.size()) {
     for (const Piece& p : ps) ((p.flags & PIECE_TRANSPOSE) ? tiles : walks).push_back(p);

@@ -64,6 +64,19 @@ def _random_workload(seed):
         rng.permutation(P).tolist()
 
 
+def _column_cases():
+    """Transposes whose overlay holds rectangles one element wide: blocks one
+    longer than the other side's, and a whole matrix of one row."""
+    for k, (dtype, op, alpha, beta) in enumerate([("f32", "T", -1.5, 0.25), ("f64", "N", 1.0, 0.0),
+                                                  ("c64", "C", 1.0, 0.0), ("c128", "C", 1 - 1j, 0.5)]):
+        a, b = ("row", "row") if op != "N" else ("row", "col")
+        A = BC(131, 97, 16, 12, 2, 2, "row", a)
+        B = BC(*((131, 97) if op == "N" else (97, 131)), 17, 17, 2, 2, "col", b)
+        yield synth.Workload(f"columns_{dtype}", dtype, [synth.Item(A, B, op, alpha, beta)], False, seed=60 + k)
+    A, B = BC(1, 300, 1, 7, 1, 2, "row", "col"), BC(1, 300, 1, 9, 1, 2, "row", "row")
+    yield synth.Workload("one_row", "f32", [synth.Item(A, B, "N", 2.0, 0.0)], False, seed=65)
+
+
 def _cases():
     for name in synth.WORKLOADS:
         yield synth.workload(name, "small"), None
@@ -73,6 +86,8 @@ def _cases():
         yield _random_workload(s)
     dtype, op, alpha, beta, A, B, sigma = many_rank_cases()[1]
     yield synth.Workload("many", dtype, [synth.Item(A, B, op, alpha, beta)], False, seed=91), sigma
+    for w in _column_cases():
+        yield w, None
 
 
 @pytest.mark.parametrize("k", range(len(list(_cases()))))
@@ -120,6 +135,14 @@ def test_direct_rectangles_reproduce_the_oracle(k):
         for r in range(P):
             assert np.array_equal(hits[i * P + r], want[r]), "an element of A is not written exactly once"
             assert np.array_equal(bufs[i * P + r].view(u), ha[r].view(u))
+
+
+@pytest.mark.parametrize("w", list(_column_cases())[:4], ids=lambda w: w.name)
+def test_columns_join_the_launch_of_tiles(w):
+    descs, keep = _descs(w)
+    x = C.costa_plan_export_direct(w.dtype, descs, None)
+    assert (x["nx"] == 1).any() and (x["nx"] > 1).any()
+    assert (x["launch"] == 0).all() and (x["flags"] & 1 == 1).all()
 
 
 @pytest.mark.parametrize("lanes", [64, 256])
