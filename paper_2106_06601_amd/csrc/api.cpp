@@ -514,18 +514,31 @@ costa_status launch_plan(State& S, costa_dtype dt, const HostPlan& hp, const Dev
   return COSTA_SUCCESS;
 }
 
+// Whether `stream` is being captured.  (The null stream reports an error while
+// another, blocking stream is: it is not captured itself.)
+bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
+
 // Puts a call's table into the plan's device copy, unless it holds it already.
-costa_status upload_table(DevicePlan& dp, const std::vector<unsigned char>& table, hipStream_t stream) {
+costa_status upload_table(DevicePlan& dp, const std::vector<unsigned char>& table, bool capturing,
+                          hipStream_t stream) {
   if (!dp.last_use) {
     if (!dp.d_table) HIP_OR_FAIL(hipMalloc(&dp.d_table, table.size()));
     if (!dp.h_staging) HIP_OR_FAIL(hipHostMalloc(&dp.h_staging, table.size(), hipHostMallocDefault));
     if (!dp.table_event) HIP_OR_FAIL(hipEventCreateWithFlags(&dp.table_event, hipEventDisableTiming));
     HIP_OR_FAIL(hipEventCreateWithFlags(&dp.last_use, hipEventDisableTiming));
   }
-  if (table == dp.last_table) return COSTA_SUCCESS;
-  // the kernels of the plan's last call read the table until they end: on
-  // another stream, the new table is written only after them
-  if (dp.used && dp.last_stream != stream) HIP_OR_FAIL(hipStreamWaitEvent(stream, dp.last_use, 0));
+  const bool same = table == dp.last_table;
+  // the plan's last call, on another stream: the table that it uploaded is
+  // there, and its kernels have read it, before this call goes on.  (A captured
+  // call that finds its table cannot wait for work outside its graph.)
+  if (dp.used && dp.last_stream != stream && !(same && capturing))
+    HIP_OR_FAIL(hipStreamWaitEvent(stream, dp.last_use, 0));
+  if (same) return COSTA_SUCCESS;
   if (dp.table_pending) HIP_OR_FAIL(hipEventSynchronize(dp.table_event));
   std::memcpy(dp.h_staging, table.data(), table.size());
   dp.last_table.clear();
@@ -578,27 +591,29 @@ costa_status transform_impl(costa_dtype dt, int32_t n, const costa_transform_des
   }
   ArgTable args;
   CallTable ct{nullptr, nullptr, (int32_t)ptr_bytes};
+  bool capturing = false;
   if (table.size() <= sizeof args) {
     std::memcpy(args.bytes, table.data(), table.size());
     ct.args = &args;
   } else {
-    st = upload_table(*dp, table, stream);
+    capturing = is_capturing(stream);
+    st = upload_table(*dp, table, capturing, stream);
     if (st != COSTA_SUCCESS) return st;
     ct.device = dp->d_table;
   }
   const ItemParam* ipar = reinterpret_cast<const ItemParam*>(table.data() + ptr_bytes);
   st = launch_plan(S, dt, hp, DeviceTables{dp->d_pieces, dp->d_tasks, dp->d_wide}, ipar, n, reads_a, aligned, ct,
                    stream, true);
+  if (ct.device && !capturing) {  // (an event recorded under capture is no use to calls outside the graph)
+    HIP_OR_FAIL(hipEventRecord(dp->last_use, stream));
+    dp->last_stream = stream;
+    dp->used = true;
+  }
   if (st != COSTA_SUCCESS) return st;
   if (ws) {
     HIP_OR_FAIL(hipEventRecord(ws->last_use, stream));
     ws->last_stream = stream;
     ws->used = true;
-  }
-  if (ct.device) {
-    HIP_OR_FAIL(hipEventRecord(dp->last_use, stream));
-    dp->last_stream = stream;
-    dp->used = true;
   }
   return COSTA_SUCCESS;
 }
