@@ -1299,9 +1299,7 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
     if (st != COSTA_SUCCESS) return st;
     const HostPlan& hp = np->host;
     unsigned char* base = dev->base;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    HIP_OR_FAIL(hipStreamIsCapturing(stream, &capture));
-    const bool capturing = capture == hipStreamCaptureStatusActive;
+    const bool capturing = is_capturing(stream);
     // the plan's tables, unless the scratch holds them already (a copy from
     // pageable host memory: the host data has been taken when the call returns,
     // or is read by the graph's copy on every replay)

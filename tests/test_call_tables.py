@@ -98,3 +98,22 @@ def test_a_captured_call_with_a_resident_table_is_accepted(standin):
     S.run(s3)
     c.check()
     S.destroy_graph(g)
+
+
+def few_ranks(S, seed=0, m=70, n=90):
+    """4 ranks: the call table travels as kernel arguments."""
+    return Call(S, seed, BC(m, n, 24, 8, 2, 2, "row", "col"), BC(m, n, 8, 16, 2, 2, "col", "col"))
+
+
+def test_a_noalloc_call_on_the_null_stream_while_another_stream_captures(standin):
+    """hipStreamIsCapturing reports an error for the null stream while a
+    blocking stream captures; the call is not part of that capture."""
+    S = standin
+    c = few_ranks(S)
+    S.refuse_implicit(1)
+    try:
+        c.run(0, "noalloc")
+    finally:
+        S.refuse_implicit(0)
+    S.run(None)
+    c.check()
