@@ -1326,8 +1326,13 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
       std::memcpy(args.bytes, table.data(), table.size());
       ct.args = &args;
     } else {
-      if (table != here.table) {
-        here.table = table;  // (kept: a captured copy reads it on every replay)
+      if (capturing) {
+        // the table itself goes into the graph, which puts it there on every
+        // replay: no host copy to keep, and no other call's table to find
+        here.table.clear();
+        HIP_OR_FAIL(launch_store_table(table.data(), table.size(), part + np->off_table, stream));
+      } else if (here.held || table != here.table) {  // (a replay may have put another table there)
+        here.table = table;
         const hipError_t e = hipMemcpyAsync(part + np->off_table, here.table.data(), table.size(),
                                             hipMemcpyHostToDevice, stream);
         if (e != hipSuccess) here.table.clear();

@@ -338,6 +338,11 @@ hipError_t launch_mover(MoverKind kind, costa_dtype dtype, const LaunchSpec& spe
                         const int32_t* tasks, int64_t ntasks, const int32_t* wide, int64_t nwide,
                         const CallTable& table, int32_t allow_wide, int32_t xcd_run, hipStream_t stream);
 
+// Writes a call's table (`bytes` a multiple of 16) to device memory with
+// kernels whose arguments carry it, kArgTableBytes each: a captured call's
+// graph then holds the table, whatever becomes of the host's copy.
+hipError_t launch_store_table(const unsigned char* table, size_t bytes, void* dst, hipStream_t stream);
+
 struct VolumeArgs {
   const Interval* rows;
   int32_t K;

@@ -13,6 +13,7 @@
 // tasks are all alike may hand each XCD (one L2) a contiguous range of them.
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <type_traits>
 
 #include "internal.hpp"
@@ -765,6 +766,16 @@ costa_tiles(ArgTable, const Piece* __restrict__ pieces, const int32_t* __restric
   }
 }
 
+// One slice of a call's table from the kernel's arguments to device memory,
+// 16 bytes a lane.
+constexpr int kStoreTableLanes = (int)(kArgTableBytes / 16);
+using Quad = unsigned __attribute__((ext_vector_type(4)));
+__global__ void __launch_bounds__(kStoreTableLanes) costa_store_table(ArgTable, Quad* __restrict__ dst, int32_t n) {
+  const Quad COSTA_CONST* src = (const Quad COSTA_CONST*)__builtin_amdgcn_kernarg_segment_ptr();
+  const int32_t i = threadIdx.x;
+  if (i < n) dst[i] = src[i];
+}
+
 // Volume of the grid overlay: every overlay block (k, l) adds its element
 // count to V[s][t] (s: owner of its cover in L(B), t: owner of its cover in
 // L(A)).  Histogram in LDS when P*P fits, flushed with 64-bit atomics.
@@ -997,6 +1008,19 @@ hipError_t launch_mover(MoverKind kind, costa_dtype dtype, const LaunchSpec& spe
     case COSTA_C64: return launch_typed<float, true>(kind, spec, l);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_store_table(const unsigned char* table, size_t bytes, void* dst, hipStream_t stream) {
+  for (size_t at = 0; at < bytes; at += kArgTableBytes) {
+    ArgTable args;
+    const size_t n = bytes - at < kArgTableBytes ? bytes - at : kArgTableBytes;
+    std::memcpy(args.bytes, table + at, n);
+    hipLaunchKernelGGL(costa_store_table, dim3(1), dim3(kStoreTableLanes), 0, stream, args,
+                       reinterpret_cast<Quad*>(static_cast<unsigned char*>(dst) + at), (int32_t)(n / 16));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_volume_dealt(const VolumeDealtArgs& a, hipStream_t stream) {

@@ -74,7 +74,7 @@ class Standin:
         for f, res, args in (("stream", vp, []), ("capture", None, [vp]), ("end_capture", vp, [vp]),
                              ("replay", None, [vp, vp]), ("nodes", ctypes.c_int, [vp]),
                              ("destroy_graph", None, [vp]), ("run", None, [vp]),
-                             ("buffer", None, [vp, ctypes.c_size_t]), ("forget", None, [vp]),
+                             ("buffer", None, [vp, ctypes.c_size_t]),
                              ("refuse_implicit", None, [ctypes.c_int]), ("faults", ctypes.c_char_p, [])):
             fn = getattr(self.lib, "standin_" + f)
             fn.restype, fn.argtypes = res, args

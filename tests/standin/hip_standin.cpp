@@ -178,8 +178,13 @@ void standin_destroy_graph(void* g) {
   delete static_cast<Graph*>(g);
 }
 void standin_run(void* s) { run_to(at((hipStream_t)s), at((hipStream_t)s).queued); }
-void standin_buffer(void* p, size_t n) { memory[(uintptr_t)p] = n; }
-void standin_forget(void* p) { memory.erase((uintptr_t)p); }
+// memory of the test (earlier buffers that it overlaps are gone)
+void standin_buffer(void* p, size_t n) {
+  const uintptr_t a = (uintptr_t)p;
+  for (auto it = memory.begin(); it != memory.end();)
+    it = it->first < a + n && a < it->first + it->second ? memory.erase(it) : std::next(it);
+  if (n) memory[a] = n;
+}
 void standin_refuse_implicit(int on) { implicit_refused = on != 0; }
 const char* standin_faults() {
   static std::string out;
@@ -363,6 +368,14 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, 
     const void* device_table = arg<const void*>(args, 4);
     const int32_t items_off = arg<int32_t>(args, 5);
     add(at(stream), [=] { move_tasks(name, table, pieces, tasks, (int64_t)grid.x, device_table, items_off); });
+  } else if (name.find("costa_store_table") != std::string::npos) {
+    const ArgTable table = arg<ArgTable>(args, 0);
+    void* dst = arg<void*>(args, 1);
+    const size_t n = (size_t)arg<int32_t>(args, 2) * 16;
+    add(at(stream), [=] {
+      if (n > sizeof table || !holds(memory, dst, n)) return fault("a stored table outside every buffer");
+      std::memcpy(dst, table.bytes, n);
+    });
   } else {
     fault("a kernel that the stand-in does not run: " + name);
   }

@@ -117,3 +117,48 @@ def test_a_noalloc_call_on_the_null_stream_while_another_stream_captures(standin
         S.refuse_implicit(0)
     S.run(None)
     c.check()
+
+
+def captured(S, call):
+    s = S.stream()
+    S.capture(s)
+    call.run(s, "noalloc")
+    return S.end_capture(s)
+
+
+def do(S, call, stream, graph=None):
+    """Runs the call, or replays its graph, and checks its result alone."""
+    if graph is None:
+        call.run(stream, "noalloc")
+    else:
+        S.replay(graph, stream)
+    S.run(stream)
+    call.check()
+
+
+@pytest.mark.parametrize("make", [few_ranks, many_ranks], ids=["table_in_arguments", "table_on_device"])
+@pytest.mark.parametrize("warm", [False, True])
+def test_captured_noalloc_calls_keep_their_buffers(standin, make, warm):
+    """Captured and uncaptured calls of one plan with different buffers in any
+    order: each replay and each call moves its own."""
+    S, s = standin, standin.stream()
+    first = make(S, 3, 61 + warm)
+    second, third = first.same_layouts(4), first.same_layouts(5)
+    if warm:
+        do(S, first, s)
+    g1 = captured(S, first)
+    do(S, first, s)  # the same buffers, before the graph has run
+    do(S, second, s)
+    do(S, first, s, g1)
+    g2 = captured(S, second)
+    do(S, first, s, g1)
+    do(S, second, s, g2)
+    do(S, third, s)
+    do(S, second, s, g2)
+    do(S, first, s, g1)
+    S.destroy_graph(g1)
+    do(S, second, s, g2)
+    do(S, third, s)
+    S.destroy_graph(g2)
+    do(S, third, s)
+    do(S, first, s)

@@ -301,3 +301,58 @@ def test_captured_noalloc_call_keeps_its_tables():
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(x, y) for x, y in zip(a, want))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("warm", [False, True])
+def test_captured_noalloc_calls_with_device_tables(warm):
+    """128 ranks: a call table too large for kernel arguments.  Captured and
+    uncaptured calls of one plan with different buffers each move their own."""
+    print(f"noalloc: captured calls, 128 ranks, warm={warm}", flush=True)
+    A, B = BC(640, 600 + warm, 12, 20, 16, 8, "row", "col"), BC(640, 600 + warm, 16, 12, 8, 16, "col", "row")
+    LA, LB = C.layout_from_spec(A), C.layout_from_spec(B)
+    calls = []
+    for _ in range(3):
+        b = [torch.rand(LB.local_elems(r), dtype=torch.float64, device="cuda") for r in range(128)]
+        a = [torch.zeros(LA.local_elems(r), dtype=torch.float64, device="cuda") for r in range(128)]
+        want = [torch.zeros_like(t) for t in a]
+        C.costa_transform("f64", "N", 1.0, 0.0, LA, want, LB, b)
+        calls.append((dict(op="N", alpha=1.0, beta=0.0, A=LA, A_local=a, B=LB, B_local=b), a, want))
+    small = C.layout_from_spec(BC(40, 40, 8, 8, 2, 2, "row", "col"))
+    x = [torch.zeros(400, dtype=torch.float64, device="cuda") for _ in range(8)]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):  # (the scratch array's address is known before the first capture)
+        C.costa_transform_batched_noalloc("f64", [dict(op="N", alpha=1.0, beta=0.0, A=small, A_local=x[:4], B=small,
+                                                       B_local=x[4:])])
+        if warm:
+            C.costa_transform_batched_noalloc("f64", [calls[0][0]])
+    torch.cuda.synchronize()
+    graphs = []
+
+    def capture(k):
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], stream=stream):
+            C.costa_transform_batched_noalloc("f64", [calls[k][0]])
+
+    def check(k, run):
+        d, a, want = calls[k]
+        for t in a:
+            t.zero_()
+        torch.cuda.synchronize()
+        run()
+        torch.cuda.synchronize()
+        assert all(torch.equal(p, q) for p, q in zip(a, want))
+
+    def eager(k):
+        check(k, lambda: C.costa_transform_batched_noalloc("f64", [calls[k][0]]))
+
+    capture(0)
+    eager(0)
+    eager(1)
+    check(0, graphs[0].replay)
+    capture(1)
+    for _ in range(2):
+        check(0, graphs[0].replay)
+        eager(2)
+        check(1, graphs[1].replay)
+    eager(0)
