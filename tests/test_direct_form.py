@@ -319,7 +319,7 @@ def test_captured_noalloc_calls_with_device_tables(warm):
         C.costa_transform("f64", "N", 1.0, 0.0, LA, want, LB, b)
         calls.append((dict(op="N", alpha=1.0, beta=0.0, A=LA, A_local=a, B=LB, B_local=b), a, want))
     small = C.layout_from_spec(BC(40, 40, 8, 8, 2, 2, "row", "col"))
-    x = [torch.zeros(400, dtype=torch.float64, device="cuda") for _ in range(8)]
+    x = [torch.zeros(small.local_elems(r % 4), dtype=torch.float64, device="cuda") for r in range(8)]
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):  # (the scratch array's address is known before the first capture)
         C.costa_transform_batched_noalloc("f64", [dict(op="N", alpha=1.0, beta=0.0, A=small, A_local=x[:4], B=small,
