@@ -287,8 +287,11 @@ costa_status costa_transform_batched(costa_dtype dtype, int32_t n, const costa_t
  * for planning and the plan cache comes from the C++ heap on the first call
  * of a (layouts, op, sigma, type) combination.
  * Every call on one device shares that device's array, which keeps the tables
- * of the last plans that fit, and those of captured calls as long as the
- * tables of all captured calls and of the current one fit together: calls that overlap on one device (on different streams, or
+ * of the last plans that fit.  Under stream capture, the plan's tables stay in
+ * the array (and a host copy of them in memory) until the graph and everything
+ * instantiated from it are destroyed, also past costa_finalize(); calls whose
+ * tables do not fit beside those of live graphs load both again each time.
+ * Calls and replays that overlap on one device (on different streams, or
  * from different threads without stream ordering) race and give undefined
  * results.  Calls on one stream are ordered by the stream. */
 #define COSTA_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)

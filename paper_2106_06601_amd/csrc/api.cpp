@@ -1110,53 +1110,118 @@ struct NoallocPlan {
   // the tables
   size_t off_tasks = 0, off_wide = 0, off_table = 0, end = 0;
   bool accepted = false;  // direct form: the message form's tables fit as well
-  bool captured = false;  // a graph holds a copy from `tables`: the plan stays in the cache
+};
+
+// A plan's part of a device's scratch array.
+struct Part {
+  size_t at, end;
+  std::shared_ptr<const NoallocPlan> plan;  // (captured copies read its tables on every replay)
+  bool loaded = false;  // its tables are there (a copy that was only captured has not run yet)
+  std::vector<unsigned char> table;  // the call table last put there (calls whose table is no kernel argument)
+  bool table_there = false;          // and it still is
+};
+
+// What a captured call's graph relies on: the part its kernels read and, where
+// that part lies over others (see NoallocDevice::beside), those parts, which
+// the graph loads again at its end.  The graph owns it (hold_in_graph).
+struct Hold {
+  std::shared_ptr<Part> own;
+  std::vector<std::shared_ptr<Part>> displaced;
 };
 
 // What one device's scratch array holds.
 struct NoallocDevice {
-  struct Resident {
-    size_t at, end;                    // the plan's part
-    bool loaded = false;               // its tables are there (a copy that was only captured has not run yet)
-    bool held = false;                 // a captured call reads it on every replay
-    std::vector<unsigned char> table;  // the call table it holds (calls whose table is no kernel argument)
-  };
   unsigned char* base = nullptr;  // address of `scratch` on the device
-  // the plans whose tables it holds, by serial: parts are handed out one
-  // after another, and start over when the next one does not fit.  Parts that
-  // captured calls read are passed over, and given up only for a plan that
-  // does not fit beside them.
-  std::map<uint64_t, Resident> resident;
+  // the parts, by their plan's serial: handed out one after another, and
+  // starting over when the next one does not fit, except that parts which a
+  // live graph holds stay
+  std::map<uint64_t, std::shared_ptr<Part>> resident;
   size_t used = 0;
+  std::vector<std::weak_ptr<Hold>> overlays;  // captured calls whose part lies over others
+  std::vector<std::shared_ptr<Hold>> kept;    // of graphs that could not take theirs
 
-  // A part of `size` bytes (at most kNoallocTableBytes, a multiple of 256).
-  size_t place(size_t size) {
-    for (int pass = 0; pass < 3; ++pass) {
+  static bool held(const std::shared_ptr<Part>& p) { return p.use_count() > 1; }
+
+  // A part for the plan, or null where the held parts leave no room.
+  std::shared_ptr<Part> place(const std::shared_ptr<NoallocPlan>& plan, size_t size) {
+    for (int pass = 0; pass < 2; ++pass) {
       if (pass > 0) {
         for (auto it = resident.begin(); it != resident.end();)
-          it = pass == 1 && it->second.held ? std::next(it) : resident.erase(it);
+          it = held(it->second) ? std::next(it) : resident.erase(it);
         used = 0;
       }
       size_t at = used;
       for (bool moved = true; moved;) {
         moved = false;
         for (const auto& kv : resident)
-          if (at < kv.second.end && kv.second.at < at + size) {
-            at = kv.second.end;
+          if (at < kv.second->end && kv.second->at < at + size) {
+            at = kv.second->end;
             moved = true;
           }
       }
       if (at + size <= kNoallocTableBytes) {
         used = at + size;
-        return at;
+        return resident.emplace(plan->serial, std::make_shared<Part>(Part{at, used, plan})).first->second;
       }
     }
-    return 0;
+    return nullptr;
+  }
+
+  // After place() found no room: a part for one call at the start of the
+  // array.  The parts it lies over (all of them held) go to `displaced`: the
+  // call loads their tables again after its kernels, so that their graphs find
+  // them.
+  std::shared_ptr<Part> beside(const std::shared_ptr<NoallocPlan>& plan, size_t size,
+                               std::vector<std::shared_ptr<Part>>& displaced) const {
+    for (const auto& kv : resident)
+      if (kv.second->at < size) displaced.push_back(kv.second);
+    return std::make_shared<Part>(Part{0, size, plan});
+  }
+
+  // Whether a replay of a live graph may leave other bytes in the part.
+  bool overlaid(const std::shared_ptr<Part>& p) {
+    bool over = false;
+    for (auto it = overlays.begin(); it != overlays.end();) {
+      const std::shared_ptr<Hold> h = it->lock();
+      if (!h) {
+        it = overlays.erase(it);
+        continue;
+      }
+      over = over || (p->at < h->own->end && h->own->at < p->end &&
+                      std::find(h->displaced.begin(), h->displaced.end(), p) == h->displaced.end());
+      ++it;
+    }
+    return over;
   }
 };
 
+void release_hold(void* p) { delete static_cast<std::shared_ptr<Hold>*>(p); }
+
+// Makes the graph that `stream` is captured into an owner of `hold`: it is
+// released when the graph and everything instantiated from it are destroyed.
+// Where the runtime does not take it, the hold is kept for good.
+void hold_in_graph(NoallocDevice& dev, const std::shared_ptr<Hold>& hold, hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  hipGraph_t graph = nullptr;
+  const hipGraphNode_t* deps = nullptr;
+  size_t ndeps = 0;
+  if (hipStreamGetCaptureInfo_v2(stream, &st, &id, &graph, &deps, &ndeps) == hipSuccess && graph) {
+    auto* mine = new std::shared_ptr<Hold>(hold);
+    hipUserObject_t object = nullptr;
+    if (hipUserObjectCreate(&object, mine, release_hold, 1, hipUserObjectNoDestructorSync) == hipSuccess) {
+      if (hipGraphRetainUserObject(graph, object, 1, hipGraphUserObjectMove) == hipSuccess) return;
+      (void)hipUserObjectRelease(object, 1);  // deletes `mine`
+    } else {
+      delete mine;
+    }
+  }
+  (void)hipGetLastError();
+  dev.kept.push_back(hold);
+}
+
 struct NoallocState {
-  std::map<std::string, std::unique_ptr<NoallocPlan>> plans;
+  std::map<std::string, std::shared_ptr<NoallocPlan>> plans;
   std::map<int, NoallocDevice> devices;
   uint64_t next_serial = 1;
 };
@@ -1187,16 +1252,15 @@ bool message_tables_fit(const NoallocPlan& dp, int es) {
 
 // The cached plan of one form of a no-allocation call, built if need be (host
 // memory only; no device call).
-NoallocPlan& noalloc_form(Form form, costa_dtype dt, const std::vector<ItemDesc>& items,
-                          const std::vector<int32_t>& sig) {
+std::shared_ptr<NoallocPlan> noalloc_form(Form form, costa_dtype dt, const std::vector<ItemDesc>& items,
+                                          const std::vector<int32_t>& sig) {
   NoallocState& N = noalloc_state();
   const int es = elem_size(dt);
   std::string key = plan_key(-1, form, es, items, sig, kNoallocMessageBytes);
   auto it = N.plans.find(key);
   if (it == N.plans.end()) {
-    if (N.plans.size() >= 64)
-      for (auto p = N.plans.begin(); p != N.plans.end();) p = p->second->captured ? std::next(p) : N.plans.erase(p);
-    std::unique_ptr<NoallocPlan> np(new NoallocPlan());
+    if (N.plans.size() >= 64) N.plans.clear();
+    std::shared_ptr<NoallocPlan> np = std::make_shared<NoallocPlan>();
     build_plan(items, sig, make_config(es, form),
                [](int64_t need) { return std::min<int64_t>(need, (int64_t)kNoallocMessageBytes); }, np->host);
     HostPlan& hp = np->host;
@@ -1221,7 +1285,7 @@ NoallocPlan& noalloc_form(Form form, costa_dtype dt, const std::vector<ItemDesc>
     std::vector<int32_t>().swap(hp.wide_tasks);
     it = N.plans.emplace(key, std::move(np)).first;
   }
-  return *it->second;
+  return it->second;
 }
 
 // The plan of a no-allocation call: the direct form where the caller's
@@ -1229,30 +1293,21 @@ NoallocPlan& noalloc_form(Form form, costa_dtype dt, const std::vector<ItemDesc>
 // accepts is decided by the message form's tables, which are planned only
 // where they might not fit.
 costa_status noalloc_plan(costa_dtype dt, const std::vector<ItemDesc>& items, const std::vector<int32_t>& sig,
-                          bool direct, NoallocPlan*& out) {
+                          bool direct, std::shared_ptr<NoallocPlan>& out) {
   if (direct) {
-    NoallocPlan& dp = noalloc_form(FORM_DIRECT, dt, items, sig);
-    out = &dp;
-    if (dp.accepted) return COSTA_SUCCESS;
+    out = noalloc_form(FORM_DIRECT, dt, items, sig);
+    if (out->accepted) return COSTA_SUCCESS;
   }
-  NoallocPlan& np = noalloc_form(FORM_MESSAGES, dt, items, sig);
-  if (np.end > kNoallocTableBytes)
-    return fail(COSTA_ERROR_NOT_SUPPORTED, "the plan's tables need " + std::to_string(np.end) +
+  const std::shared_ptr<NoallocPlan> np = noalloc_form(FORM_MESSAGES, dt, items, sig);
+  if (np->end > kNoallocTableBytes)
+    return fail(COSTA_ERROR_NOT_SUPPORTED, "the plan's tables need " + std::to_string(np->end) +
                                                " bytes; the no-allocation scratch holds " +
                                                std::to_string(kNoallocTableBytes) +
                                                " bytes of tables (costa_transform_batched has no such limit)");
-  if ((size_t)np.host.workspace_bytes > kNoallocMessageBytes)
+  if ((size_t)np->host.workspace_bytes > kNoallocMessageBytes)
     return fail(COSTA_ERROR_NOT_SUPPORTED, "a wave's messages exceed the no-allocation scratch");
-  out = &np;
-  if (!direct) return COSTA_SUCCESS;
-  // (planning the message form may have started the cache over)
-  NoallocPlan& dp = noalloc_form(FORM_DIRECT, dt, items, sig);
-  if (dp.end <= kNoallocTableBytes) {
-    dp.accepted = true;
-    out = &dp;
-  } else {
-    out = &noalloc_form(FORM_MESSAGES, dt, items, sig);
-  }
+  if (direct && out->end <= kNoallocTableBytes) out->accepted = true;
+  else out = np;
   return COSTA_SUCCESS;
 }
 
@@ -1291,7 +1346,7 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
     // is refused before any device call
     const int32_t P = items[0].A->nranks;
     const bool direct = !a_overlaps_b(elem_size(dtype), n, desc, items, sig, P);
-    NoallocPlan* np = nullptr;
+    std::shared_ptr<NoallocPlan> np;
     st = noalloc_plan(dtype, items, sig, direct, np);
     if (st != COSTA_SUCCESS) return st;
     NoallocDevice* dev = nullptr;
@@ -1300,52 +1355,72 @@ extern "C" costa_status costa_transform_batched_noalloc(costa_dtype dtype, int32
     const HostPlan& hp = np->host;
     unsigned char* base = dev->base;
     const bool capturing = is_capturing(stream);
-    // the plan's tables, unless the scratch holds them already (a copy from
+    const size_t size = align256(np->end);  // at most kNoallocTableBytes, itself a multiple of 256
+    auto found = dev->resident.find(np->serial);
+    std::shared_ptr<Part> here = found != dev->resident.end() ? found->second : dev->place(np, size);
+    std::vector<std::shared_ptr<Part>> displaced;
+    if (!here) here = dev->beside(np, size, displaced);
+    // (one owner is the map, or nothing, and one is `here`)
+    const bool held = here.use_count() > 2, overlaid = dev->overlaid(here);
+    if (capturing) {
+      std::shared_ptr<Hold> hold = std::make_shared<Hold>(Hold{here, displaced});
+      hold_in_graph(*dev, hold, stream);
+      if (!displaced.empty()) dev->overlays.push_back(hold);
+    }
+    // a part's tables, unless the scratch holds them already (a copy from
     // pageable host memory: the host data has been taken when the call returns,
     // or is read by the graph's copy on every replay)
-    auto res = dev->resident.find(np->serial);
-    if (res == dev->resident.end()) {
-      const size_t size = align256(np->end), at = dev->place(size);
-      res = dev->resident.emplace(np->serial, NoallocDevice::Resident{at, at + size}).first;
-    }
-    NoallocDevice::Resident& here = res->second;
-    if (!here.loaded) {
-      if (!np->tables.empty())
-        HIP_OR_FAIL(hipMemcpyAsync(base + here.at, np->tables.data(), np->tables.size(), hipMemcpyHostToDevice, stream));
-      here.loaded = !capturing;
-    }
-    if (capturing) here.held = np->captured = true;
-    unsigned char* part = base + here.at;
-    std::vector<unsigned char> table;
-    std::vector<char> reads_a;
-    bool aligned = true;
-    const size_t ptr_bytes = call_table(dtype, n, desc, P, base + kNoallocTableBytes, table, reads_a, aligned);
-    ArgTable args;
-    CallTable ct{nullptr, nullptr, (int32_t)ptr_bytes};
-    if (table.size() <= sizeof args) {
-      std::memcpy(args.bytes, table.data(), table.size());
-      ct.args = &args;
-    } else {
-      if (capturing) {
-        // the table itself goes into the graph, which puts it there on every
-        // replay: no host copy to keep, and no other call's table to find
-        here.table.clear();
-        HIP_OR_FAIL(launch_store_table(table.data(), table.size(), part + np->off_table, stream));
-      } else if (here.held || table != here.table) {  // (a replay may have put another table there)
-        here.table = table;
-        const hipError_t e = hipMemcpyAsync(part + np->off_table, here.table.data(), table.size(),
-                                            hipMemcpyHostToDevice, stream);
-        if (e != hipSuccess) here.table.clear();
-        HIP_OR_FAIL(e);
+    auto load = [&](const Part& p) -> costa_status {
+      if (!p.plan->tables.empty())
+        HIP_OR_FAIL(hipMemcpyAsync(base + p.at, p.plan->tables.data(), p.plan->tables.size(), hipMemcpyHostToDevice,
+                                   stream));
+      return COSTA_SUCCESS;
+    };
+    auto enqueue = [&]() -> costa_status {
+      if (!here->loaded || overlaid) {
+        here->loaded = false;
+        const costa_status lst = load(*here);
+        if (lst != COSTA_SUCCESS) return lst;
+        here->loaded = !capturing && !overlaid;
       }
-      ct.device = part + np->off_table;
+      unsigned char* part = base + here->at;
+      std::vector<unsigned char> table;
+      std::vector<char> reads_a;
+      bool aligned = true;
+      const size_t ptr_bytes = call_table(dtype, n, desc, P, base + kNoallocTableBytes, table, reads_a, aligned);
+      ArgTable args;
+      CallTable ct{nullptr, nullptr, (int32_t)ptr_bytes};
+      if (table.size() <= sizeof args) {
+        std::memcpy(args.bytes, table.data(), table.size());
+        ct.args = &args;
+      } else {
+        ct.device = part + np->off_table;
+        if (capturing) {
+          // the table itself goes into the graph, which puts it there on every
+          // replay: no host copy to keep, and no other call's table to find
+          here->table_there = false;
+          HIP_OR_FAIL(launch_store_table(table.data(), table.size(), part + np->off_table, stream));
+        } else if (!here->table_there || table != here->table) {
+          here->table_there = false;
+          here->table = table;
+          HIP_OR_FAIL(hipMemcpyAsync(part + np->off_table, here->table.data(), table.size(), hipMemcpyHostToDevice,
+                                     stream));
+          here->table_there = !held && !overlaid;  // else a replay may put another one there
+        }
+      }
+      const ItemParam* ipar = reinterpret_cast<const ItemParam*>(table.data() + ptr_bytes);
+      const DeviceTables tabs{reinterpret_cast<const Piece*>(part),
+                              reinterpret_cast<const int32_t*>(part + np->off_tasks),
+                              reinterpret_cast<const int32_t*>(part + np->off_wide)};
+      // no timing events on this path (creating one may allocate)
+      return launch_plan(S, dtype, hp, tabs, ipar, n, reads_a, aligned, ct, stream, false);
+    };
+    st = enqueue();
+    for (const std::shared_ptr<Part>& p : displaced) {
+      const costa_status again = load(*p);
+      if (st == COSTA_SUCCESS) st = again;
     }
-    const ItemParam* ipar = reinterpret_cast<const ItemParam*>(table.data() + ptr_bytes);
-    const DeviceTables tabs{reinterpret_cast<const Piece*>(part),
-                            reinterpret_cast<const int32_t*>(part + np->off_tasks),
-                            reinterpret_cast<const int32_t*>(part + np->off_wide)};
-    // no timing events on this path (creating one may allocate)
-    return launch_plan(S, dtype, hp, tabs, ipar, n, reads_a, aligned, ct, stream, false);
+    return st;
   });
 }
 
@@ -1398,8 +1473,10 @@ extern "C" costa_status costa_finalize(void) {
       S.plans.clear();
       S.host_plans.clear();
       N.plans.clear();
-      for (auto& kv : N.devices) {  // the scratch arrays stay (static); what they hold is forgotten
-        kv.second.resident.clear();
+      for (auto& kv : N.devices) {  // the scratch arrays stay (static); what no graph reads there is forgotten
+        auto& parts = kv.second.resident;
+        for (auto it = parts.begin(); it != parts.end();)
+          it = NoallocDevice::held(it->second) ? std::next(it) : parts.erase(it);
         kv.second.used = 0;
       }
       for (auto& kv : S.ws) {

@@ -162,3 +162,95 @@ def test_captured_noalloc_calls_keep_their_buffers(standin, make, warm):
     S.destroy_graph(g2)
     do(S, third, s)
     do(S, first, s)
+
+
+def large_plan(S, seed, rows):
+    """About `rows` / 180 MiB of tables (rectangles of one to six elements)."""
+    return Call(S, seed, BC(rows, 200, 2, 3, 2, 2, "row", "col"), BC(rows, 200, 3, 2, 2, 2, "col", "col"))
+
+
+def test_graphs_whose_tables_fill_the_scratch_array(standin):
+    """Captured calls hold about 11 of the 16 MiB of tables; calls that find
+    no room beside them, captured or not, leave every graph's tables in place,
+    and every call finds its own."""
+    S, s = standin, standin.stream()
+    a, b, c, d = (large_plan(S, 7 + k, 900 + 100 * k) for k in range(4))
+    do(S, a, s)
+    ga = captured(S, a)  # relies on the tables that the call before it loaded
+    gb = captured(S, b)  # holds a copy of its own
+    for call in (a, b):
+        do(S, call, s, ga if call is a else gb)
+    do(S, c, s)          # no room for c, nor for d
+    do(S, a, s, ga)
+    do(S, c, s)
+    do(S, b, s, gb)
+    do(S, a, s)
+    gd = captured(S, d)
+    for _ in range(2):
+        do(S, d, s, gd)
+        do(S, a, s, ga)
+        do(S, c, s)
+        do(S, b, s)
+        do(S, b, s, gb)
+    S.destroy_graph(ga)
+    S.destroy_graph(gb)
+    do(S, c, s)          # its part may now lie where gd's replays load theirs
+    do(S, d, s, gd)
+    do(S, c, s)
+    gc = captured(S, c)
+    do(S, d, s, gd)
+    do(S, c, s, gc)
+    S.destroy_graph(gd)
+    do(S, a, s)
+    do(S, c, s, gc)
+    S.destroy_graph(gc)
+    for call in (a, b, c, d, a):
+        do(S, call, s)
+
+
+def test_graphs_keep_their_plans_past_the_plan_cache_and_finalize(standin):
+    """70 other plans start the plan cache over, and costa_finalize drops it:
+    a captured call's replays still find their tables."""
+    S, s = standin, standin.stream()
+    c = few_ranks(S, 11, 50, 60)
+    cold = captured(S, c)
+    do(S, c, s)
+    warm = captured(S, c)
+    others = [few_ranks(S, 12, 20, 100 + k) for k in range(70)]
+    for o in others:
+        do(S, o, s)
+    do(S, c, s, warm)
+    do(S, c, s, cold)
+    S.C.costa_finalize()
+    for o in others:
+        do(S, o, s)
+    do(S, c, s, warm)
+    do(S, c, s, cold)
+    do(S, c, s)
+    S.destroy_graph(cold)
+    S.destroy_graph(warm)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_captured_and_uncaptured_noalloc_calls_in_random_order(standin, seed):
+    S, s = standin, standin.stream()
+    rng = np.random.default_rng(seed)
+    calls = [large_plan(S, 20 + k, 600 + 250 * k + seed) for k in range(4)] + \
+        [many_ranks(S, 30 + k, 70 + 10 * k + seed) for k in range(2)] + [few_ranks(S, 40, 30 + seed)]
+    calls += [c.same_layouts(50 + k) for k, c in enumerate(calls[3:])]
+    graphs = []
+    for _ in range(120):
+        what = rng.random()
+        if what < 0.2 and len(graphs) < 5:
+            k = int(rng.integers(len(calls)))
+            graphs.append((calls[k], captured(S, calls[k])))
+        elif what < 0.3 and graphs:
+            S.destroy_graph(graphs.pop(int(rng.integers(len(graphs))))[1])
+        elif what < 0.65 and graphs:
+            do(S, graphs[0][0], s, graphs[0][1])
+            call, g = graphs[int(rng.integers(len(graphs)))]
+            do(S, call, s, g)
+        else:
+            do(S, calls[int(rng.integers(len(calls)))], s)
+    for _, g in graphs:
+        S.destroy_graph(g)
