@@ -870,8 +870,10 @@ costa_status volume_dealt(const Layout& A, const Layout& B, bool tr, int64_t* V_
     const Dim &f = b_fine ? db : da, &c = b_fine ? da : db;
     VolumeAxis& x = a.axis[d];
     x.n = d == 0 ? A.nrows : A.ncols;
-    x.fine = VolumeSide{f.off, f.blk, f.np, f.src};
-    x.coarse = VolumeSide{c.off, c.blk, c.np, c.src};
+    // (a block may be far longer than the matrix: cut at the window's end, so
+    // that no position past it is larger than twice that)
+    x.fine = VolumeSide{f.off, std::min(f.blk, f.off + x.n), f.np, f.src};
+    x.coarse = VolumeSide{c.off, std::min(c.blk, c.off + x.n), c.np, c.src};
     x.nblocks = f.nblocks;
     x.fine_is_b = b_fine ? 1 : 0;
     x.nclass = da.np;
@@ -880,11 +882,12 @@ costa_status volume_dealt(const Layout& A, const Layout& B, bool tr, int64_t* V_
     if (nhist > kVolumeHistMax) return COSTA_SUCCESS;
   }
   if (P > kVolumeRanksMax) return COSTA_SUCCESS;
-  // (positions and block ends up to one block past the window, plus a source process)
+  // (positions and block ends up to one block past the window, plus a source
+  // process; blk is at most off + n)
   a.narrow = 1;
   for (const VolumeAxis& x : a.axis)
     for (const VolumeSide& q : {x.fine, x.coarse})
-      if (q.off + x.n + 2 * q.blk + q.src > (int64_t)INT32_MAX) a.narrow = 0;
+      if (q.off + x.n > INT32_MAX || q.off + x.n + 2 * q.blk + q.src > (int64_t)INT32_MAX) a.narrow = 0;
   a.nhist = (int32_t)nhist;
   a.P = P;
   done = true;

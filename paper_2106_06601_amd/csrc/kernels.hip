@@ -16,7 +16,7 @@
 #include <cstring>
 #include <type_traits>
 
-#include "internal.hpp"
+#include "index_math.hpp"
 
 // Products and sums are rounded one by one, never fused into an FMA, so the
 // results are reproducible bit for bit.
@@ -835,27 +835,6 @@ struct Launch {
 constexpr int kVolumeThreads = 1024;
 constexpr int kVolumeOneGroup = 16384;
 
-template <typename I>
-__device__ __forceinline__ void count_overlaps(const VolumeAxis& x, unsigned long long* h, int32_t first,
-                                               int32_t step) {
-  const I off = (I)x.fine.off, blk = (I)x.fine.blk, coff = (I)x.coarse.off, cblk = (I)x.coarse.blk, n = (I)x.n;
-  const I fnp = (I)x.fine.np, fsrc = (I)x.fine.src, cnp = (I)x.coarse.np, csrc = (I)x.coarse.src;
-  const I k0 = off / blk;  // the window's first block in the dealt dimension
-  for (int32_t k = first; k < x.nblocks; k += step) {
-    const I b = k0 + (I)k;
-    I i = max(off, b * blk) - off;  // in the window
-    const I end = min(off + n, (b + 1) * blk) - off;
-    const int32_t pf = (int32_t)((b + fsrc) % fnp);
-    while (i < end) {
-      const I cb = (coff + i) / cblk;
-      const I stop = min(end, (cb + 1) * cblk - coff);
-      const int32_t pc = (int32_t)((cb + csrc) % cnp);
-      atomicAdd(&h[x.fine_is_b ? pf * x.nclass + pc : pc * x.nclass + pf], (unsigned long long)(stop - i));
-      i = stop;
-    }
-  }
-}
-
 __global__ void __launch_bounds__(kVolumeThreads) costa_volume_dealt(VolumeDealtArgs a) {
   __shared__ unsigned long long h[kVolumeHistMax];
   __shared__ int16_t cls[4 * kVolumeRanksMax];
@@ -871,8 +850,10 @@ __global__ void __launch_bounds__(kVolumeThreads) costa_volume_dealt(VolumeDealt
   for (int32_t d = one ? 0 : blockIdx.y; d <= (one ? 1 : (int32_t)blockIdx.y); ++d) {
     const VolumeAxis& x = a.axis[d];
     const int32_t first = blockIdx.x * kVolumeThreads + tid, step = gridDim.x * kVolumeThreads;
-    if (a.narrow) count_overlaps<uint32_t>(x, h + x.hist0, first, step);
-    else count_overlaps<uint64_t>(x, h + x.hist0, first, step);
+    unsigned long long* hx = h + x.hist0;
+    auto add = [hx](int32_t entry, unsigned long long elems) { atomicAdd(&hx[entry], elems); };
+    if (a.narrow) count_overlaps<uint32_t>(x, first, step, add);
+    else count_overlaps<uint64_t>(x, first, step, add);
   }
   __syncthreads();
   if (!one) {

@@ -75,3 +75,16 @@ def test_volume_of_dealt_layouts(name, mapped):
         assert np.array_equal(C.costa_volume_matrix(A, B, op), want)
     assert C.costa_volume_matrix(G, G, "N").tolist() == [[11, 0], [0, 9]]  # the overlay kernel in between
     assert np.array_equal(C.costa_volume_matrix(A, B, op), want)
+
+
+@pytest.mark.parametrize("big", [2**31 - 1, 2**33 - 1, 2**62, 2**63 - 1])
+def test_volume_of_blocks_longer_than_the_matrix(big):
+    """(block size 2^62: its low 32 bits are zero)"""
+    print(f"volume, blocks of {big}", flush=True)
+    m, n = 97, 60
+    for a, b in ((big, 5), (8, big), (big, big)):
+        A = C.Layout.block_cyclic(m, n, a, 7, 3, 2, "row", "col")
+        B = C.Layout.block_cyclic(m, n, b, 9, 3, 2, "row", "col")
+        hr, hc = _count(m, (a, 3, 0, 0), (b, 3, 0, 0)), _count(n, (7, 2, 0, 0), (9, 2, 0, 0))
+        want = np.einsum("ij,kl->ikjl", hr, hc).reshape(6, 6)
+        assert np.array_equal(C.costa_volume_matrix(A, B, "N"), want)
