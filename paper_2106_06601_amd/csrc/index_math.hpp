@@ -13,11 +13,11 @@ namespace costa {
 // I holds every position up to one block past the window (see
 // VolumeDealtArgs::narrow).
 template <typename I, typename Add>
-COSTA_BOTH void count_overlaps(const VolumeAxis& x, int32_t first, int32_t step, Add&& add) {
+COSTA_BOTH void count_overlaps(const VolumeAxis& x, uint32_t first, uint32_t step, Add&& add) {
   const I off = (I)x.fine.off, blk = (I)x.fine.blk, coff = (I)x.coarse.off, cblk = (I)x.coarse.blk, n = (I)x.n;
   const I fnp = (I)x.fine.np, fsrc = (I)x.fine.src, cnp = (I)x.coarse.np, csrc = (I)x.coarse.src;
   const I k0 = off / blk;  // the window's first block in the dealt dimension
-  for (int32_t k = first; k < x.nblocks; k += step) {
+  for (uint32_t k = first; k < (uint32_t)x.nblocks; k += step) {  // (unsigned: k may pass 2^31 by a step)
     const I b = k0 + (I)k;
     const I start = b * blk, stop_f = (b + 1) * blk;
     I i = (off > start ? off : start) - off;  // in the window

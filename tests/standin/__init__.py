@@ -75,7 +75,8 @@ class Standin:
                              ("replay", None, [vp, vp]), ("nodes", ctypes.c_int, [vp]),
                              ("destroy_graph", None, [vp]), ("run", None, [vp]),
                              ("buffer", None, [vp, ctypes.c_size_t]),
-                             ("refuse_implicit", None, [ctypes.c_int]), ("faults", ctypes.c_char_p, [])):
+                             ("refuse_implicit", None, [ctypes.c_int]),
+                             ("lane_volume", ctypes.c_int64, [ctypes.c_int32] * 3), ("faults", ctypes.c_char_p, [])):
             fn = getattr(self.lib, "standin_" + f)
             fn.restype, fn.argtypes = res, args
             setattr(self, f, fn)

@@ -204,6 +204,27 @@ void standin_buffer(void* p, size_t n) {
     it = it->first < a + n && a < it->first + it->second ? memory.erase(it) : std::next(it);
   if (n) memory[a] = n;
 }
+// Elements that one lane of the volume kernel counts on an axis of n blocks of
+// one element each, or -1 where it leaves its range.
+int64_t standin_lane_volume(int32_t n, int32_t first, int32_t step) {
+  VolumeAxis x{};
+  x.n = n;
+  x.fine = VolumeSide{0, 1, 1, 0};
+  x.coarse = VolumeSide{0, n, 1, 0};
+  x.nblocks = n;
+  x.nclass = 1;
+  int64_t sum = 0, rounds = 0;
+  struct Left {};
+  try {
+    count_overlaps<uint32_t>(x, first, step, [&](int32_t, unsigned long long e) {
+      sum += (int64_t)e;
+      if (++rounds > n / step + 1) throw Left();
+    });
+  } catch (const Left&) {
+    return -1;
+  }
+  return sum;
+}
 void standin_refuse_implicit(int on) { implicit_refused = on != 0; }
 const char* standin_faults() {
   static std::string out;

@@ -37,3 +37,11 @@ def test_blocks_longer_than_the_matrix(standin, big, side):
     V = C.costa_volume_matrix(A, B, "N", stream=S.stream())
     S.check()
     assert np.array_equal(V, want)
+
+
+@pytest.mark.parametrize("n", [5, 65536, 65537, 2**31 - 65536, 2**31 - 65535, 2**31 - 2])
+def test_a_lane_ends_at_the_last_block(standin, n):
+    """64 workgroups of 1024 lanes step through up to 2^31 - 2 blocks."""
+    step = 65536
+    for first in (0, 1, step - 1):
+        assert standin.lane_volume(n, first, step) == max(0, -(-(n - first) // step))
