@@ -263,3 +263,24 @@ def test_parallel_host_fill_equals_the_oracle_fill(dtype):
     b = np.zeros(n, dtype=oracle.NUMPY[dtype])
     oracle.fill(dtype, b, 99, synth.stream(synth.ROLE_A, 5, 3))
     assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
+
+
+def test_buffers_are_asked_for_their_addresses():
+    """Tensors, integers, None and any object with a data_ptr() method, also a
+    tensor type with its own."""
+    torch = pytest.importorskip("torch")
+
+    class Own(torch.Tensor):
+        def data_ptr(self):
+            return 4096
+
+    class Other:
+        def data_ptr(self):
+            return np.int64(8192)
+
+    t = torch.zeros(3)
+    for bufs, want in (([t, t[1:]], [t.data_ptr(), t.data_ptr() + 4]), ([t.as_subclass(Own), t], [4096, t.data_ptr()]),
+                       ([Other(), None, 256], [8192, 0, 256]), ([Other(), t], [8192, t.data_ptr()])):
+        keep = []
+        at = C._pointers(bufs, keep)
+        assert list((ctypes.c_uint64 * len(bufs)).from_address(at)) == want
