@@ -11,15 +11,18 @@
 #include <new>
 #include <string>
 
+#include "index_math.hpp"
 #include "plan.hpp"
 
 namespace costa {
 namespace {
 
-// Rectangles are cut at 4M elements: the kernels index a rectangle's
-// elements in 32 bits and compute row and column from a float estimate of
-// the quotient, exact up to one correction step below 2^24 units.
+// Rectangles are cut at 4M elements: the kernels index a rectangle's elements
+// in 32 bits, and find row and column from a float estimate of the quotient
+// that is exact for the units of one rectangle and of its last task past them.
 constexpr int64_t kMaxPieceElems = 1 << 22;
+static_assert(kMaxPieceElems + kWideTaskUnits <= kDivmodUnits, "divmod holds for every unit of a task");
+static_assert(kStackWaveTasksMax < kDivmodUnits2, "divmod holds for every wave task of a stack");
 
 int elem_size(costa_dtype d) {
   switch (d) {

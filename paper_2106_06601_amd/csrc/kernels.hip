@@ -52,24 +52,6 @@ constexpr int kShortTileColumn = 384, kShortTileRow = 256;
 
 constexpr int kThreads = kThreadsPerTask;
 
-// The task of workgroup b of n.  Workgroups are dispatched round-robin over
-// the 8 XCDs (b % 8 is b's XCD).  run 0: task b.  run -1: XCD x takes the
-// x-th of 8 contiguous ranges of tasks, workgroup b the (b/8)-th task of its
-// XCD's range.  run k > 0: the XCDs take runs of k consecutive tasks in turn
-// (tasks past the last whole round of runs: task b).
-__device__ __forceinline__ int32_t xcd_order(int32_t b, int32_t n, int32_t run) {
-  constexpr int32_t X = 8;
-  if (run == 0) return b;
-  const int32_t xcd = b % X, idx = b / X;
-  if (run > 0) {
-    const int32_t turn = idx / run;
-    return (turn + 1) * X * run > n ? b : (turn * X + xcd) * run + idx - turn * run;
-  }
-  const int32_t q = n / X, r = n % X;
-  const int32_t start = xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q;
-  return start + idx;
-}
-
 template <typename S, int N>
 struct alignas(sizeof(S) * N) Vec {
   S v[N];
@@ -178,51 +160,6 @@ struct TypeTraits {
   static constexpr int ES = (int)sizeof(S) * NS;  // bytes per element
   static constexpr int WIDE_NEL = wide_elems(ES); // elements per 16-byte unit
   static constexpr bool NT_WALK = COSTA_NT_LOADS && ES <= COSTA_NT_LOADS_MAX_ES;
-};
-
-// y = u / n and x = u - y*n for 0 <= u < 2^23, n >= 1 (n >= 2 from 2^22 on):
-// the estimate u * rcp(n) is off by at most 1.5 * 2^-23 of the quotient (rcp
-// to 1 ulp, one rounding of the product), less than one, so one step each way
-// makes it exact.  Selects, not loops: the corrections cost two instructions
-// each and no branch.
-__device__ __forceinline__ void divmod(int32_t u, int32_t n, int32_t& y, int32_t& x) {
-  y = (int32_t)((float)u * __builtin_amdgcn_rcpf((float)n));
-  x = u - y * n;
-  const bool under = x < 0;
-  y = under ? y - 1 : y;
-  x = under ? x + n : x;
-  const bool over = x >= n;
-  y = over ? y + 1 : y;
-  x = over ? x - n : x;
-}
-
-// A lane's way through the rows (`len` elements each) of a tile, T
-// elements a step: the element's memory offset (row * ld + column) and its
-// LDS slot (row * ls + column * lc).  One division places the lane; every
-// step then adds the same two amounts, and one more where the step passes a
-// row's end (a step passes at most one: T % len < len).
-template <int T>
-struct TileWalk {
-  int32_t col, len, rem, lds, dlds, wlds;
-  int64_t off, doff, woff;
-  __device__ __forceinline__ TileWalk(int32_t tid, int32_t len_, int64_t ld, int32_t ls, int32_t lc) : len(len_) {
-    int32_t q, row;
-    divmod(T, len, q, rem);
-    divmod(tid, len, row, col);
-    off = (int64_t)row * ld + col;
-    doff = (int64_t)q * ld + rem;
-    woff = ld - len;
-    lds = row * ls + col * lc;
-    dlds = q * ls + rem * lc;
-    wlds = ls - len * lc;
-  }
-  __device__ __forceinline__ void next() {
-    col += rem;
-    const bool wrap = col >= len;
-    col -= wrap ? len : 0;
-    off += doff + (wrap ? woff : 0);
-    lds += dlds + (wrap ? wlds : 0);
-  }
 };
 
 // Row walk: dst[y*dst_ld + x] = f(src[y*src_ld + x]).  The task starts at

@@ -76,7 +76,11 @@ class Standin:
                              ("destroy_graph", None, [vp]), ("run", None, [vp]),
                              ("buffer", None, [vp, ctypes.c_size_t]),
                              ("refuse_implicit", None, [ctypes.c_int]),
-                             ("lane_volume", ctypes.c_int64, [ctypes.c_int32] * 3), ("faults", ctypes.c_char_p, [])):
+                             ("lane_volume", ctypes.c_int64, [ctypes.c_int32] * 3),
+                             ("divmod", None, [ctypes.c_int, vp, vp, vp, vp, ctypes.c_int64]),
+                             ("xcd_order", None, [ctypes.c_int32, ctypes.c_int32, vp]),
+                             ("tile_walk", None, [ctypes.c_int32] * 3 + [ctypes.c_int64] + [ctypes.c_int32] * 3 +
+                              [vp, vp]), ("faults", ctypes.c_char_p, [])):
             fn = getattr(self.lib, "standin_" + f)
             fn.restype, fn.argtypes = res, args
             setattr(self, f, fn)

@@ -225,6 +225,26 @@ int64_t standin_lane_volume(int32_t n, int32_t first, int32_t step) {
   }
   return sum;
 }
+// The kernels' index arithmetic (index_math.hpp).
+void standin_divmod(int ulps, const int32_t* u, const int32_t* n, int32_t* y, int32_t* x, int64_t count) {
+  reciprocal_ulps = ulps;
+  for (int64_t i = 0; i < count; ++i) divmod(u[i], n[i], y[i], x[i]);
+  reciprocal_ulps = 0;
+}
+void standin_xcd_order(int32_t n, int32_t run, int32_t* out) {
+  for (int32_t b = 0; b < n; ++b) out[b] = xcd_order(b, n, run);
+}
+void standin_tile_walk(int32_t lanes, int32_t tid, int32_t len, int64_t ld, int32_t ls, int32_t lc, int32_t steps,
+                       int64_t* off, int32_t* slot) {
+  auto walk = [&](auto w) {
+    for (int32_t k = 0; k < steps; ++k, w.next()) {
+      off[k] = w.off;
+      slot[k] = w.lds;
+    }
+  };
+  if (lanes == kSmallTileLanes) walk(TileWalk<kSmallTileLanes>(tid, len, ld, ls, lc));
+  else walk(TileWalk<kThreadsPerTask>(tid, len, ld, ls, lc));
+}
 void standin_refuse_implicit(int on) { implicit_refused = on != 0; }
 const char* standin_faults() {
   static std::string out;

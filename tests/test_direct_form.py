@@ -145,65 +145,6 @@ def test_columns_join_the_launch_of_tiles(w):
     assert (x["launch"] == 0).all() and (x["flags"] & 1 == 1).all()
 
 
-@pytest.mark.parametrize("lanes", [64, 256])
-def test_lanes_step_through_every_tile_element(lanes):
-    """A lane's steps (one division, then the same additions, and one more
-    past a row's end) visit every element of a tile once, at the memory offset
-    and LDS slot of its row and column."""
-    for rows, length in [(1, 1), (2, 3), (7, 64), (64, 7), (23, 37), (3, 255), (2, 257), (5, 300), (1, 1024), (128, 16)]:
-        ld, ls, lc = 1000003, length | 1, 1
-        q, rem = divmod(lanes, length)
-        seen = np.zeros((rows, length), int)
-        for tid in range(lanes):
-            row, col = divmod(tid, length)
-            off, slot = row * ld + col, row * ls + col * lc
-            for k in range(-(-rows * length // lanes)):
-                if k * lanes + tid < rows * length:
-                    r, c = off // ld, off % ld
-                    assert slot == r * ls + c * lc
-                    seen[r, c] += 1
-                col += rem
-                wrap = col >= length
-                col -= length if wrap else 0
-                off += q * ld + rem + (ld - length if wrap else 0)
-                slot += q * ls + rem * lc + (ls - length * lc if wrap else 0)
-        assert (seen == 1).all()
-
-
-def test_division_by_reciprocal_needs_one_step():
-    """The kernels' u / n: float(u) * rcp(n), truncated, is at most one off
-    for u < 2^22 + 1024 (row walks, tiles) and, for n >= 2, for u < 2^23
-    (stacks), with the reciprocal anywhere within one ulp."""
-    rng = np.random.default_rng(5)
-    for top, first in (((1 << 22) + 1024, 1), (1 << 23, 2)):
-        n = np.concatenate([np.arange(first, 3000), rng.integers(first, top, 3000)]).astype(np.int64)
-        base = np.float32(1) / n.astype(np.float32)
-        for k in (1, 2, 3, 1 << 10, 1 << 20, 1 << 30):
-            m = np.minimum(np.minimum(k, (top - 1) // n) * n, top - 1)  # multiples of n, and the last ones
-            for u in (m, np.maximum(m - 1, 0), np.minimum(m + 1, top - 1)):
-                for rcp in (base, np.nextafter(base, np.float32(0)), np.nextafter(base, np.float32(2))):
-                    y = (u.astype(np.float32) * rcp).astype(np.int64)
-                    assert (np.abs(y - u // n) <= 1).all()
-
-
-@pytest.mark.parametrize("run", [-1, 0, 16])
-def test_workgroup_order_is_a_permutation(run):
-    for n in (1, 7, 8, 127, 128, 129, 1000, 4096, 4100):
-        out = []
-        for b in range(n):
-            xcd, idx = b % 8, b // 8
-            if run == 0:
-                t = b
-            elif run > 0:
-                turn = idx // run
-                t = b if (turn + 1) * 8 * run > n else (turn * 8 + xcd) * run + idx - turn * run
-            else:
-                q, r = n // 8, n % 8
-                t = (xcd * (q + 1) if xcd < r else r * (q + 1) + (xcd - r) * q) + idx
-            out.append(t)
-        assert sorted(out) == list(range(n))
-
-
 # ---------------------------------------------------------------------------
 # GPU
 # ---------------------------------------------------------------------------
