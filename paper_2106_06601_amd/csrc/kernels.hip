@@ -883,7 +883,10 @@ hipError_t go_tiles(const Launch& l) {
 template <typename S, bool CPLX, int KIND, int MODE, bool CONJ>
 hipError_t go(const Launch& l, int tile_lanes) {
   if (tile_lanes == 0) return go_walks<S, CPLX, KIND, MODE, CONJ>(l);
-  if (tile_lanes == kSmallTileLanes) return go_tiles<S, CPLX, KIND, MODE, CONJ, kSmallTileLanes>(l);
+  if (tile_lanes == kSmallTileLanes) {  // (planned for the direct form alone)
+    if constexpr (KIND == KIND_DIRECT) return go_tiles<S, CPLX, KIND, MODE, CONJ, kSmallTileLanes>(l);
+    else return hipErrorInvalidValue;
+  }
   return go_tiles<S, CPLX, KIND, MODE, CONJ, kThreads>(l);
 }
 
