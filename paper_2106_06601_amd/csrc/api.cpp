@@ -731,8 +731,7 @@ static costa_status export_form(Form form, costa_dtype dtype, int32_t n, const c
           }
         o.wide_ntasks = lr.nwide ? wend - q.aux : 0;
         o.launch = launch;
-        o.reserved = 0;
-
+        o.reserved = form == FORM_DIRECT ? lr.tile_lanes : 0;
       }
       ++launch;
     };

@@ -50,7 +50,9 @@ void build_plan(const std::vector<ItemDesc>& items, const std::vector<int32_t>& 
 }  // namespace costa
 
 // costa_plan_export() of the direct form: its rectangles, all DIRECT (the
-// transposed ones in a launch of their own, first, where both kinds occur).
+// transposed ones in a launch of their own, first, where both kinds occur),
+// with the lanes of a workgroup of their launch's tiles in `reserved` (0 in
+// launches of row walks).
 // For host-side checking of plans; not part of the public header.
 extern "C" costa_status costa_plan_export_direct(costa_dtype dtype, int32_t n, const costa_transform_desc* desc,
                                                  const int32_t* sigma, costa_piece_info* out, int64_t capacity,

@@ -21,21 +21,24 @@ BC, GEN, SL = synth.BlockCyclic, synth.General, synth.ScaLapack
 
 # elements and width of the tiles that one wave moves (launches of small tiles)
 SMALL, SMALL_X = {4: 1024, 8: 768, 16: 512}, 64
+BUDGET = {4: 4096, 8: 2048, 16: 3072}  # of 256-lane tiles
 
 
 def check_tiles(ps, es):
     """A launch of tiles: workgroups numbered in rectangle order, one per
-    tile, and every tile within the limits of its launch's workgroups (256
-    lanes, or one wave)."""
-    shapes = [(int(p["tile_x"]), int(p["tile_y"])) for p in ps]
-    small = all(x <= SMALL_X and x * y <= SMALL[es] for x, y in shapes)
+    tile, and every tile within the limits (elements, width, LDS array) of the
+    launch's workgroups, of one wave or of 256 lanes."""
+    lanes = int(ps[0]["reserved"])
+    assert lanes in (64, 256)
+    budget, lds, maxx = (SMALL[es], SMALL[es] + SMALL_X, SMALL_X) if lanes == 64 else (BUDGET[es], CAP[es], MAXX[es])
     nxt = 0
-    for p, (x, y) in zip(ps, shapes):
-        nx, ny = int(p["nx"]), int(p["ny"])
-        assert int(p["flags"]) & 1 and 1 <= x <= nx and 1 <= y <= ny
-        assert x * (y | 1) <= (SMALL[es] + SMALL_X if small else CAP[es]) and x <= MAXX[es]
+    for p in ps:
+        nx, ny, x, y = int(p["nx"]), int(p["ny"]), int(p["tile_x"]), int(p["tile_y"])
+        assert int(p["flags"]) & 1 and 1 <= x <= nx and 1 <= y <= ny and int(p["reserved"]) == lanes
+        assert x <= maxx and x * y <= budget and x * (y | 1) <= lds
         assert int(p["group"]) == nxt and int(p["ntasks"]) == -(-nx // x) * -(-ny // y)
         nxt += int(p["ntasks"])
+    return lanes
 
 
 def _random_workload(seed):
@@ -102,6 +105,7 @@ def test_direct_rectangles_reproduce_the_oracle(k):
         if int(ps[0]["flags"]) & 1:
             check_tiles(ps, es)
             continue
+        assert all(int(p["reserved"]) == 0 for p in ps)
         check_tasks(ps, es)
         assert all((cv == 1).all() for cv in stack_walk_cover(ps, es).values())
     sg = list(range(P)) if sigma is None else sigma
@@ -135,6 +139,18 @@ def test_direct_rectangles_reproduce_the_oracle(k):
         for r in range(P):
             assert np.array_equal(hits[i * P + r], want[r]), "an element of A is not written exactly once"
             assert np.array_equal(bufs[i * P + r].view(u), ha[r].view(u))
+
+
+@pytest.mark.parametrize("dtype", ["f64", "c128", "f32", "c64"])
+def test_both_tile_kernels_are_planned(dtype):
+    """Blocks of 12 elements move in tiles of one wave, blocks of 256 in tiles
+    of 256 lanes."""
+    for block, lanes in ((12, 64), (256, 256)):
+        A, B = BC(1024, 768, block, block, 2, 2, "row", "row"), BC(768, 1024, block, block, 2, 2, "col", "row")
+        w = synth.Workload("b", dtype, [synth.Item(A, B, "T", 2.0, 0.5)], False, seed=70)
+        descs, keep = _descs(w)
+        x = C.costa_plan_export_direct(dtype, descs, None)
+        assert check_tiles([p for p in x if p["launch"] == 0], synth.ITEMSIZE[dtype]) == lanes
 
 
 @pytest.mark.parametrize("w", list(_column_cases())[:4], ids=lambda w: w.name)
