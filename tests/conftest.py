@@ -31,3 +31,16 @@ def oracle_lib():
     import oracle
     oracle.lib()
     return oracle
+
+
+@pytest.fixture
+def form(request):
+    """The form that transforms take in a test: "direct" (the default), or
+    "messages" (their kernels are timed)."""
+    if request.param == "messages":
+        import paper_2106_06601_amd as C
+        C.costa_timing_enable(C.TIMING_MESSAGES)
+        yield request.param
+        C.costa_timing_enable(False)
+    else:
+        yield request.param

@@ -21,6 +21,11 @@ if torch.cuda.is_available():
 BC, GEN = synth.BlockCyclic, synth.General
 
 
+def both_forms(test):
+    """Runs a test in the direct form and in the message form."""
+    return pytest.mark.usefixtures("form")(pytest.mark.parametrize("form", ["direct", "messages"], indirect=True)(test))
+
+
 def _say(msg):
     print(msg, flush=True)
 
@@ -69,6 +74,7 @@ def test_volume_matrix_full_size_closed_forms():
 # ---------------------------------------------------------------------------
 # the five workloads
 # ---------------------------------------------------------------------------
+@both_forms
 @pytest.mark.parametrize("name", synth.WORKLOADS)
 def test_workload_small_full_compare(name):
     w = synth.workload(name, "small")
@@ -85,6 +91,7 @@ def test_workload_small_full_compare(name):
         case.check_full()
 
 
+@both_forms
 @pytest.mark.parametrize("name", ["reshuffle_transpose_1k", "blocksize_change_16k", "scaled_transpose_20k",
                                   "cosma_complex_16k"])
 def test_workload_full_size_sampled(name):
@@ -105,6 +112,7 @@ def test_workload_full_size_sampled(name):
     case.free()
 
 
+@both_forms
 def test_workload_rpa_full_size_sampled():
     w = synth.workload("rpa_batched_tall_skinny")
     need = sum(2 * it.A.nrows * it.A.ncols * 8 for it in w.items)
@@ -128,10 +136,12 @@ def test_workload_rpa_full_size_sampled():
     case.free()
 
 
+@both_forms
 def test_launches_beyond_one_slice():
-    """A launch of more than 2^23 workgroups runs in slices: two ranks swap the
-    halves of a 69632^2 fp64 matrix (38.8 GB, 4.85e9 elements, every element
-    remote: about 9.5 million workgroups per pack and unpack launch)."""
+    """A launch of more than 2^23 workgroups runs in slices: two ranks swap and
+    scale the halves of a 69632^2 fp64 matrix (38.8 GB, 4.85e9 elements, every
+    element remote: about 9.5 million workgroups in the launch that scales; a
+    copying launch takes half of that)."""
     M = N = 69632
     need = 3 * M * N * 8
     torch.cuda.empty_cache()
@@ -140,13 +150,12 @@ def test_launches_beyond_one_slice():
         pytest.skip(f"needs {need / 2**30:.0f} GiB; {free / 2**30:.0f} GiB free")
     A = GEN(M, N, [0, M], [0, N // 2, N], [0, 1], 2, "col")
     B = GEN(M, N, [0, M], [0, N // 2, N], [1, 0], 2, "col")
-    w = synth.Workload("slices", "f64", [synth.Item(A, B, "N", 1.0, 0.0)], False, seed=77)
-    descs = [dict(op="N", alpha=1.0, beta=0.0, A=C.layout_from_spec(A), B=C.layout_from_spec(B))]
-    x = C.costa_plan_export("f64", descs)
-    for kind in (0, 1):  # pack, unpack
-        sel = x[x["kind"] == kind]
-        assert int(sel["group"].max()) + 1 > 1 << 23
-    _say("transform 69632^2 swap, two launch slices")
+    w = synth.Workload("slices", "f64", [synth.Item(A, B, "N", 2.0, 0.0)], False, seed=77)
+    descs = [dict(op="N", alpha=2.0, beta=0.0, A=C.layout_from_spec(A), B=C.layout_from_spec(B))]
+    for export, kind in ((C.costa_plan_export_direct, 2), (C.costa_plan_export, 1)):
+        x = export("f64", descs)
+        assert int(x["group"][x["kind"] == kind].max()) + 1 > 1 << 23
+    _say("transform 69632^2 scaled swap, two launch slices")
     case = Case(w, a_init="nan")
     case.run()
     assert case.check_sampled(n_random=100000, n_corners=100000) > 100000
@@ -181,6 +190,7 @@ SCALARS = [(1.0, 0.0), (2.0, 0.5), (-0.75, 1.25), (0.3, 0.0), (1.0, 1.0)]
 CSCALARS = [(1.0, 0.0), (0.5 - 0.25j, 0.25 + 1j), (1 + 0j, 1 + 0j), (0.3 + 0.7j, 0.0)]
 
 
+@both_forms
 @pytest.mark.parametrize("dtype", ["f64", "c128", "f32", "c64"])
 def test_random_layouts_full_compare(dtype):
     rng = np.random.default_rng({"f64": 1, "c128": 2, "f32": 3, "c64": 4}[dtype])
@@ -203,6 +213,7 @@ def test_random_layouts_full_compare(dtype):
         case.check_full()
 
 
+@both_forms
 @pytest.mark.parametrize("dtype", ["f64", "c128", "f32", "c64"])
 def test_random_larger_layouts_full_compare(dtype):
     """Random layouts large enough that rectangles span many tasks, several
@@ -238,6 +249,7 @@ def test_random_larger_layouts_full_compare(dtype):
         case.free()
 
 
+@both_forms
 @pytest.mark.parametrize("k", [0, 1])
 def test_many_virtual_ranks_full_compare(k):
     dtype, op, alpha, beta, A, B, sigma = many_rank_cases()[k]
@@ -249,6 +261,7 @@ def test_many_virtual_ranks_full_compare(k):
     case.free()
 
 
+@both_forms
 def test_random_batched_full_compare():
     rng = np.random.default_rng(11)
     for case_no in range(6):
@@ -270,6 +283,7 @@ def test_random_batched_full_compare():
         case.check_full()
 
 
+@both_forms
 @pytest.mark.parametrize("dtype", ["f64", "c128", "f32", "c64"])
 def test_transposed_rectangles_around_the_tile_limits(dtype):
     """Transposed rectangles whose width and height sit on both sides of every
@@ -301,6 +315,7 @@ def test_transposed_rectangles_around_the_tile_limits(dtype):
 # ---------------------------------------------------------------------------
 # edge cases
 # ---------------------------------------------------------------------------
+@both_forms
 @pytest.mark.parametrize("k", range(5))
 def test_short_row_walks_full_compare(k):
     """Row walks of 4-64 elements starting inside 128-byte lines (16-byte
@@ -315,6 +330,7 @@ def test_short_row_walks_full_compare(k):
     case.check_full()
 
 
+@both_forms
 @pytest.mark.parametrize("k", range(5))
 def test_stacked_walks_full_compare(k):
     """Row walks moved as stacks (rectangles that follow one another along a
@@ -329,6 +345,7 @@ def test_stacked_walks_full_compare(k):
     case.check_full()
 
 
+@both_forms
 @pytest.mark.parametrize("seed", range(8))
 def test_random_stacked_layouts_full_compare(seed):
     """Random ScaLAPACK-descriptor pairs whose walks stack (sizes, pads, first
@@ -342,6 +359,7 @@ def test_random_stacked_layouts_full_compare(seed):
     case.check_full()
 
 
+@both_forms
 def test_stacks_longer_than_the_limit_full_compare():
     """Stacks cut at 4096 rectangles (local columns of 70,000 rows in 16-row
     source blocks), every element compared."""
@@ -368,6 +386,7 @@ def test_waves_with_tiny_workspace():
         C.costa_set_workspace_limit(0)
 
 
+@both_forms
 def test_degenerate_shapes():
     cases = [
         (GEN(1, 1, [0, 1], [0, 1], [0], 1, "col"), GEN(1, 1, [0, 1], [0, 1], [0], 1, "row"), "T"),
@@ -391,6 +410,7 @@ def test_empty_matrix_is_a_no_op():
     torch.cuda.synchronize()
 
 
+@both_forms
 def test_unaligned_buffers_take_the_narrow_path():
     """Buffers offset by one element (8 bytes) are not 16-byte aligned."""
     it = synth.workload("blocksize_change_16k", "small").items[0]
@@ -413,6 +433,8 @@ def test_unaligned_buffers_take_the_narrow_path():
         assert np.array_equal(dA[r][1:].cpu().numpy(), hA[r])
 
 
+@pytest.mark.usefixtures("form")
+@pytest.mark.parametrize("form", ["messages"], indirect=True)
 def test_two_streams_share_the_workspace_safely():
     w = synth.workload("blocksize_change_16k", "small")
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
@@ -428,8 +450,11 @@ def test_two_streams_share_the_workspace_safely():
     torch.cuda.synchronize()
     c1.check_full()
     c2.check_full()
+    st = C.costa_plan_stats(w.dtype, [dict(op=w.items[0].op, alpha=1.0, beta=0.0, A=c1.LA[0], B=c1.LB[0])])
+    assert st["workspace_bytes"] > 0
 
 
+@both_forms
 def test_host_threads_call_at_once():
     """Eight host threads call the library at the same moment (the binding
     releases the interpreter lock during each call), each with its own stream
@@ -469,18 +494,25 @@ def test_host_threads_call_at_once():
         c.check_full()
 
 
-@pytest.mark.parametrize("kind", ["messages", "direct_only"])
+@pytest.mark.usefixtures("form")
+@pytest.mark.parametrize("kind,form", [("messages", "messages"), ("direct_only", "direct"),
+                                       ("device_table", "direct")], indirect=["form"])
 def test_one_plan_two_streams_different_buffers(kind):
     """Two calls of one cached plan with different buffers, on two streams,
     issued back to back while the first call's kernels still run (full
     16384^2 sizes): the second call's buffer table must not reach the first
     call's kernels.  direct_only: a plan without message buffers (the same
-    layout for A and B), where nothing else orders the two calls."""
+    layout for A and B).  device_table: 128 ranks, whose table is too large
+    for kernel arguments, so that both calls use the plan's device copy."""
     if kind == "messages":
         w = synth.workload("blocksize_change_16k")
-    else:
+    elif kind == "direct_only":
         L = BC(16384, 16384, 256, 256, 4, 4, "row", "col")
         w = synth.Workload("same_layout", "f64", [synth.Item(L, L, "N", 2.0, 0.5)], False, seed=33)
+    else:
+        w = synth.Workload("many", "f64", [synth.Item(BC(16384, 16384, 256, 256, 16, 8, "row", "col"),
+                                                      BC(16384, 16384, 128, 128, 8, 16, "row", "col"), "N", 2.0, 0.5)],
+                           False, seed=34)
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
     with torch.cuda.stream(s1):
         c1 = Case(w, sigma=None)

@@ -4,8 +4,10 @@ The allocation-free entry point keeps its plan tables and message buffers in
 the library's static scratch array.  Each case runs both entry points on the
 same seeded inputs (two copies of A with the same initial contents) and
 compares every element bit for bit; consecutive calls change the plan the
-scratch array holds (a large plan in many waves, then smaller ones, then the
-first again with other buffers).
+scratch array holds (a large plan, then smaller ones, then the first again
+with other buffers).  These take the direct form; calls whose A and B buffers
+share memory take the message form, here in many waves of the scratch array's
+message area.
 """
 import pytest
 import torch
@@ -67,13 +69,9 @@ class Twin:
 
 
 def test_noalloc_matches_the_allocating_entry_point():
-    C = lib()
-    # 1) the block-size change at full size: 1.6 GB of messages, many waves of
-    #    the scratch array's message area; relabeling on
+    # 1) the block-size change at full size, relabeling on
     _say("noalloc: blocksize_change_16k full size")
     big = Twin("blocksize_change_16k")
-    stats = C.costa_plan_stats(big.w.dtype, big.descs(big.case.A), big.case.sigma)
-    assert stats["message_bytes"] > C.NOALLOC_SCRATCH_BYTES  # needs several waves there
     big.run_and_compare()
     # 2) a smaller input right after it: the scaled transpose (alpha = 2,
     #    beta = 0.5: A is read) at reduced size, then the 1024^2 transpose
@@ -94,3 +92,34 @@ def test_noalloc_matches_the_allocating_entry_point():
     big = Twin("blocksize_change_16k")
     big.run_and_compare()
     big.free()
+
+
+@pytest.mark.parametrize("name", ["copy", "transpose"])
+def test_noalloc_messages_in_waves(name):
+    """A and B of each rank interleaved in one buffer (A in the upper half of
+    every column or row, B in the lower): the calls take the message form, in
+    five waves or more; each against the direct form on buffers that share
+    nothing."""
+    C = lib()
+    n, P = 6144, 16
+    op, alpha, beta = ("N", 1.0, 0.0) if name == "copy" else ("T", 2.0, 0.5)
+    _say(f"noalloc: messages in waves, {name}")
+    LA, LB = (C.layout_from_spec(synth.ScaLapack(n, n, b, b, 0, 0, 2 * (n // 4), 4, 4, "row")) for b in (256, 128))
+    one = [torch.rand(2 * (n // 4) * (n // 4), dtype=torch.float64, device="cuda") for _ in range(P)]
+    upper, lower = (lambda t: t.view(n // 4, 2, n // 4)[:, 0]), (lambda t: t.view(n // 4, 2, n // 4)[:, 1])
+    sep_a, sep_b = [t.clone() for t in one], [torch.zeros_like(t) for t in one]
+    for t, b in zip(one, sep_b):
+        upper(b).copy_(lower(t))
+    before = [t.clone() for t in one]
+    at = lambda bufs, off: [t.data_ptr() + 8 * off for t in bufs]  # noqa: E731
+    d = dict(op=op, alpha=alpha, beta=beta, A=LA, B=LB)
+    stats = C.costa_plan_stats("f64", [dict(d)])
+    assert stats["message_bytes"] > 4 * (C.NOALLOC_SCRATCH_BYTES - (16 << 20))  # the message area, a wave
+    C.costa_transform_batched("f64", [dict(d, A_local=at(sep_a, 0), B_local=at(sep_b, 0))])
+    for _ in range(2):
+        for t, b in zip(one, before):
+            t.copy_(b)
+        C.costa_transform_batched_noalloc("f64", [dict(d, A_local=at(one, 0), B_local=at(one, n // 4))])
+        torch.cuda.synchronize()
+        for t, a, b in zip(one, sep_a, before):
+            assert torch.equal(_bytes(upper(t)), _bytes(upper(a))) and torch.equal(_bytes(lower(t)), _bytes(lower(b)))
