@@ -267,7 +267,7 @@ def test_parallel_host_fill_equals_the_oracle_fill(dtype):
 
 def test_buffers_are_asked_for_their_addresses():
     """Tensors, integers, None and any object with a data_ptr() method, also a
-    tensor type with its own."""
+    tensor type with its own; few and many."""
     torch = pytest.importorskip("torch")
 
     class Own(torch.Tensor):
@@ -280,7 +280,10 @@ def test_buffers_are_asked_for_their_addresses():
 
     t = torch.zeros(3)
     for bufs, want in (([t, t[1:]], [t.data_ptr(), t.data_ptr() + 4]), ([t.as_subclass(Own), t], [4096, t.data_ptr()]),
-                       ([Other(), None, 256], [8192, 0, 256]), ([Other(), t], [8192, t.data_ptr()])):
+                       ([Other(), None, 256], [8192, 0, 256]), ([Other(), t], [8192, t.data_ptr()]),
+                       ([t, t[2:]] * 10, [t.data_ptr(), t.data_ptr() + 8] * 10),
+                       ([t] * 19 + [t.as_subclass(Own)], [t.data_ptr()] * 19 + [4096]),
+                       ([t] * 19 + [None], [t.data_ptr()] * 19 + [0])):
         keep = []
         at = C._pointers(bufs, keep)
         assert list((ctypes.c_uint64 * len(bufs)).from_address(at)) == want
