@@ -41,7 +41,8 @@ def kernel_source_hash() -> str:
     h = hashlib.sha256()
     # the kernels and what decides their launches (rectangles, groups, order)
     for f in ("paper_2106_06601_amd/csrc/kernels.hip", "paper_2106_06601_amd/csrc/internal.hpp",
-              "paper_2106_06601_amd/csrc/plan.cpp", "paper_2106_06601_amd/csrc/api.cpp"):
+              "paper_2106_06601_amd/csrc/index_math.hpp", "paper_2106_06601_amd/csrc/plan.cpp",
+              "paper_2106_06601_amd/csrc/api.cpp"):
         with open(os.path.join(ROOT, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -437,8 +438,9 @@ def summarize_profiles(src: str, out_dir: str = None) -> None:
             rows = list(csv.DictReader(fh))
         lines = [f"# Kernel trace: {_title(name)}", "", "Command (from /tmp with TMPDIR=/tmp, on one MI355X):", "",
                  "```", *profile_commands(name, "trace"), "```", "",
-                 "Each transform kernel: 1 plan-building call + 20 warm-up + 20 timed steps (times the launches per "
-                 "step).", _TEMPLATE_NOTE, "",
+                 "Direct kernels: 1 plan-building call + 20 warm-up + 20 timed steps; pack and unpack-transform: 1 "
+                 "plan-building call + 3 warm-up + 20 timed steps of the message form (times the launches per step).",
+                 _TEMPLATE_NOTE, "",
                  "| kernel | role | calls | average (us) | min (us) | max (us) | share |",
                  "|---|---|---|---|---|---|---|"]
         for r in rows:
@@ -546,21 +548,15 @@ def summarize_profiles(src: str, out_dir: str = None) -> None:
         with open(path, "w") as fh:
             fh.write("\n".join(lines))
         wrote.append(path)
-    # LDS bank conflicts and occupancy (also of the odd-height tile variant)
+    # LDS bank conflicts and occupancy
     sections = []
-    for prefix, name in [("lds", n) for n in LDS_WORKLOADS] + [("ldsodd", n) for n in LDS_WORKLOADS]:
-        pl = os.path.join(src, f"{prefix}_{name}")
+    for name in LDS_WORKLOADS:
+        pl = os.path.join(src, f"lds_{name}")
         if not os.path.isdir(pl):
             continue
         V = _pmc_values(pl)
         M = {c: _per_kernel_mean(V[c]) for c in PMC_LDS.split()}
-        cmds = profile_commands(name, "lds")
-        head = f"## {_title(name)}"
-        if prefix == "ldsodd":
-            head = f"## Variant with odd tile heights (COSTA_ODD_TILES=1): {_title(name)}"
-            cmds = ["python3 <repo>/paper_2106_06601_amd/build.py --define COSTA_ODD_TILES=1 --out <lib>"] + \
-                   [f"COSTA_LIB=<lib> {c.replace(f'lds_{name}', f'ldsodd_{name}')}" for c in cmds]
-        sec = [head, "", "```", *cmds, "```", "",
+        sec = [f"## {_title(name)}", "", "```", *profile_commands(name, "lds"), "```", "",
                "| kernel | dispatches | SQ_INSTS_LDS | SQ_LDS_BANK_CONFLICT | conflicts per LDS instruction | "
                "SQ_WAVES | SQ_WAVE_CYCLES | GRBM_GUI_ACTIVE | resident waves per CU |",
                "|---|---|---|---|---|---|---|---|---|"]
