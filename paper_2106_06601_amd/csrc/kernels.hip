@@ -893,7 +893,7 @@ hipError_t go(const Launch& l, int tile_lanes) {
 template <typename S, bool CPLX, int KIND>
 hipError_t go_mode(const Launch& l, const LaunchSpec& spec) {
   // one mode for the whole call: its own kernel (the per-pair kernel holds
-  // the registers of every mode: float tiles 86 against 50, five waves per
+  // the registers of every mode: float tiles 83 against 64, five waves per
   // SIMD against eight)
   const int conj = spec.conj, tl = spec.tile_lanes;
   if (spec.mode == MODE_COPY)
