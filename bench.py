@@ -527,9 +527,15 @@ def summarize_profiles(src: str, out_dir: str = None) -> None:
                       "figure of the same run; calibrated bytes = counter x 1024 x the copy's factor):", "",
                   "| kind | launches | FETCH+WRITE bytes per launch | ratio | DRAM read+write bytes per launch | "
                   "ratio | algorithmic bytes per launch |", "|---|---|---|---|---|---|---|"]
-        for k, (n, sf, sw, sdr, sdw) in kinds.items():
+        for k, (dispatches, sf, sw, sdr, sdw) in kinds.items():
             if k not in dA["kernels"]:  # launches the timed steps do not make
                 continue
+            # (a launch of more than 2^23 workgroups is several dispatches)
+            steps = 1 + dA["warmup"] + dA["steps"] if k == "direct" else \
+                1 + min(dA["warmup"], 3) + min(dA["steps"], 20)
+            n = round(steps * dA["kernels"][k]["launches_per_step"])
+            if dispatches < n:
+                raise RuntimeError(f"{name}: {dispatches} {k} dispatches for {n} launches")
             hbm = round((sf / n * ff + sw / n * wf) * 1024)
             dram = round((sdr / n * drf + sdw / n * dwf) * 1024)
             alg = dA["kernels"][k]["bytes_per_launch"]
